@@ -112,7 +112,8 @@ const char *llg_last_error(const llg_solver *s);
  * periodic (its length must then be a product of 2, 3, 5, 7);
  * `pbc_images` (>= 0) periodic images are added per periodic axis on each
  * side.  Open axes are zero padded to an FFT length >= 2n made of the
- * factors 2, 3, 5, 7 (Sec. 3.3).  Invalidates m and the demag kernel.
+ * factors 2, 3, 5, 7 (Sec. 3.3): the shortest one, or the next one with
+ * compiled kernels.  Invalidates m and the demag kernel.
  * LLG_E_UNSUPPORTED if a padded length exceeds the library's limits
  * (x: 2048, y and z: 4096; x up to 4096 for one-cell-thick films whose
  * padded y length has a compiled column kernel, e.g. 2048 x 2048).
@@ -287,8 +288,8 @@ llg_status llg_kernel_bytes(llg_solver *s, double *bytes_out, int n_kinds);
  * pair cannot serve this geometry; ms_out may be NULL, n_out its length) and
  * the chosen pair in choice[0..1] (may be NULL).  Results of different
  * variants differ by FP32 rounding (each is checked against the FP64 oracle
- * to 1e-5).  LLG_E_UNSUPPORTED unless the geometry is 2D with compiled
- * lengths.  llg_set_variants sets the solver's pair, and the table's
+ * to 1e-5).  LLG_E_UNSUPPORTED unless the geometry is 2D and its shortest
+ * padded lengths are compiled.  llg_set_variants sets the solver's pair, and the table's
  * defaults for its lengths, directly (LLG_E_ARG if the pair cannot serve the
  * geometry). */
 llg_status llg_autotune(llg_solver *s, int iters, double *ms_out, int n_out, int *choice);
@@ -341,11 +342,11 @@ llg_status llg_demag_tensor(llg_solver *s, const int32_t *offsets, int64_t count
  * single-film solver (same kernels, same order), so results do not depend
  * on the batch composition.  Each axis of a film is zero padded to the
  * shortest compiled FFT length >= 2 n (x: 64, 128, 192, 256, 384, 512, 768,
- * 1024, 2048, 4096; y: twice 32, 64, 96, 128, 192, 256, 384, 512, 1024,
- * 2048), which leaves the convolution unchanged (Sec. 3.2 needs only
- * >= 2 n - 1); where that is also the single-film solver's padding (sides
- * 32, 64, 96, 128, 192, 256, 384, 512, 1024, 2048) a batched film equals
- * the single-film run bit for bit.  Sides beyond 2048 give
+ * 1024, 1536, 2048, 4096; y: twice 32, 64, 96, 128, 192, 256, 384, 512,
+ * 768, 1024, 2048), which leaves the convolution unchanged (Sec. 3.2 needs
+ * only >= 2 n - 1); where that is also the single-film solver's padding
+ * (sides 32, 64, 96, 128, 192, 256, 384, 512, 768, 1024, 2048 among them) a
+ * batched film equals the single-film run bit for bit.  Sides beyond 2048 give
  * LLG_E_UNSUPPORTED.
  */
 typedef struct llg_batch llg_batch;

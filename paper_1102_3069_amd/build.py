@@ -1,5 +1,6 @@
 """Builds the HIP library libllg.so in-tree for gfx950 with hipcc: each
-source is compiled to an object in parallel, then they are linked."""
+source is compiled to an object in parallel (the 2D kernels in several
+parts), then they are linked."""
 import os
 import subprocess
 import sys
@@ -10,7 +11,9 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libllg.so")
-SOURCES = ["kernels.hip", "fast2d.hip", "fast3d.hip", "tensor.hip", "solver.hip", "batch.hip", "surrogate.hip"]
+SOURCES = ["fast2d.hip", "kernels.hip", "fast3d.hip", "tensor.hip", "solver.hip", "batch.hip", "surrogate.hip"]
+# sources compiled once per part of their kernel variants: (macro, parts)
+PARTS = {"fast2d.hip": ("FAST2D_PART", 5)}
 
 
 def hipcc():
@@ -26,9 +29,11 @@ FLAGS = [
 ]
 
 
-def _compile(src, verbose):
-    obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
-    cmd = [hipcc()] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(unit, verbose):
+    src, part = unit
+    obj = os.path.join(OBJ, os.path.splitext(src)[0] + ("" if part is None else f"_{part}") + ".o")
+    define = [] if part is None else [f"-D{PARTS[src][0]}={part}"]
+    cmd = [hipcc()] + FLAGS + define + ["-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -43,9 +48,10 @@ def _compile(src, verbose):
 
 def build(verbose=True):
     os.makedirs(OBJ, exist_ok=True)
-    jobs = min(len(SOURCES), max(1, min(8, os.cpu_count() or 1)))
+    units = [(src, part) for src in SOURCES for part in (range(PARTS[src][1]) if src in PARTS else (None,))]
+    jobs = min(len(units), max(1, min(8, os.cpu_count() or 1)))
     with ThreadPoolExecutor(jobs) as ex:
-        objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
+        objs = list(ex.map(lambda u: _compile(u, verbose), units))
     tmp = LIB + ".tmp"
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     # roctx ranges around the API calls (rocprofv3 --marker-trace)

@@ -1257,16 +1257,35 @@ __global__ __launch_bounds__((ColSplit<L, E, NQ>::NT)) void col2d_fast(Col2dArgs
 // variant in use for a length comes from a process-wide table that
 // llg_autotune fills (variant 0 until then).
 // ---------------------------------------------------------------------------
+// The kernels of a part of the variants are compiled in an object of their
+// own (this file once per FAST2D_PART, in parallel); part 0 holds the
+// dispatch.
+#ifndef FAST2D_PART
+#define FAST2D_PART 0
+#endif
+constexpr int kParts = 5;
 // rows: (Px, elements per lane, frequency classes, variant)
-#define ROW_VARIANTS(X) X(64, 4, 2, 0) X(64, 8, 2, 1) X(128, 4, 2, 0) X(128, 4, 4, 1) X(192, 12, 2, 0)    \
-    X(192, 6, 2, 1) X(256, 4, 2, 0) X(256, 4, 4, 1) X(384, 12, 2, 0) X(384, 6, 4, 1) X(512, 4, 2, 0)    \
-    X(512, 4, 4, 1) X(768, 12, 2, 0) X(768, 6, 4, 1) X(1024, 8, 2, 0) X(1024, 4, 4, 1) X(2048, 8, 4, 0)  \
-    X(2048, 16, 2, 1) X(4096, 16, 4, 0) X(4096, 32, 2, 1)
+#define ROW_VARIANTS_0(X)
+#define ROW_VARIANTS_1(X) X(64, 4, 2, 0) X(64, 8, 2, 1) X(128, 4, 2, 0) X(128, 4, 4, 1) X(192, 12, 2, 0)  \
+    X(192, 6, 2, 1) X(256, 4, 2, 0) X(256, 4, 4, 1)
+#define ROW_VARIANTS_2(X) X(384, 12, 2, 0) X(384, 6, 4, 1) X(512, 4, 2, 0) X(512, 4, 4, 1) X(768, 12, 2, 0) \
+    X(768, 6, 4, 1)
+#define ROW_VARIANTS_3(X) X(1024, 8, 2, 0) X(1024, 4, 4, 1) X(1536, 12, 4, 0) X(1536, 12, 2, 1)
+#define ROW_VARIANTS_4(X) X(2048, 8, 4, 0) X(2048, 16, 2, 1) X(4096, 16, 4, 0) X(4096, 32, 2, 1)
 // columns: (L = Py/2, elements per lane, frequency classes, variant)
-#define COL_VARIANTS(X) X(32, 4, 2, 0) X(32, 8, 2, 1) X(64, 4, 2, 0) X(64, 4, 4, 1) X(96, 12, 2, 0)        \
-    X(96, 6, 2, 1) X(128, 4, 2, 0) X(128, 4, 4, 1) X(192, 12, 2, 0) X(192, 6, 4, 1) X(256, 4, 2, 0)       \
-    X(256, 4, 4, 1) X(384, 12, 2, 0) X(384, 6, 4, 1) X(512, 8, 2, 0) X(512, 4, 4, 1) X(1024, 16, 2, 0)    \
-    X(1024, 8, 4, 1) X(2048, 16, 4, 0) X(2048, 32, 2, 1)
+#define COL_VARIANTS_0(X) X(32, 4, 2, 0) X(32, 8, 2, 1) X(64, 4, 2, 0) X(64, 4, 4, 1) X(96, 12, 2, 0)      \
+    X(96, 6, 2, 1) X(128, 4, 2, 0) X(128, 4, 4, 1) X(192, 12, 2, 0) X(192, 6, 4, 1) X(256, 4, 2, 0)        \
+    X(256, 4, 4, 1)
+#define COL_VARIANTS_1(X) X(384, 12, 2, 0) X(384, 6, 4, 1)
+#define COL_VARIANTS_2(X) X(512, 8, 2, 0) X(512, 4, 4, 1)
+#define COL_VARIANTS_3(X) X(768, 12, 2, 0) X(768, 6, 4, 1) X(1024, 16, 2, 0) X(1024, 8, 4, 1)
+#define COL_VARIANTS_4(X) X(2048, 16, 4, 0) X(2048, 32, 2, 1)
+#define ROW_VARIANTS(X) ROW_VARIANTS_0(X) ROW_VARIANTS_1(X) ROW_VARIANTS_2(X) ROW_VARIANTS_3(X) ROW_VARIANTS_4(X)
+#define COL_VARIANTS(X) COL_VARIANTS_0(X) COL_VARIANTS_1(X) COL_VARIANTS_2(X) COL_VARIANTS_3(X) COL_VARIANTS_4(X)
+#define CAT2(a, b) a##b
+#define CAT(a, b) CAT2(a, b)
+#define PART_ROW_VARIANTS CAT(ROW_VARIANTS_, FAST2D_PART)
+#define PART_COL_VARIANTS CAT(COL_VARIANTS_, FAST2D_PART)
 
 // grouped launches: one launch runs a pass for all films of one length
 // class (same compiled variant); block b works on film map[b].x, local
@@ -1304,9 +1323,38 @@ constexpr int kMaxLds = 160 * 1024;
 // kernels whose dynamic LDS may exceed 64 KB need the limit raised once
 static hipError_t allow_lds(const void* kernel, int bytes) { return raise_lds_limit(kernel, bytes); }
 
+}  // namespace
+
+// the launches of one part's variants (hipErrorInvalidValue: not among them)
+template <int PART>
+struct Fast2dPart {
+    static hipError_t row_fwd(const Grid& g, const float2* twx, float2* S, const FwdArgs& fa, DevState* st,
+                              hipStream_t s, bool nat);
+    static hipError_t row_inv(const Grid& g, const Phys& p, const float2* twx, float2* S, const StageArgs& sa,
+                              DevState* st, hipStream_t s, bool nat);
+    static hipError_t col(const Col2dArgs& a, DevState* st, hipStream_t s);
+    static hipError_t row_fwd_group(int Px, int var, const FilmRow* films, const int2* map, int nblocks, hipStream_t s);
+    static hipError_t row_inv_group(int Px, int var, const FilmRow* films, const int2* map, int nblocks, hipStream_t s);
+    static hipError_t col_group(int L, int var, const FilmCol* films, const int2* map, int nblocks, hipStream_t s);
+};
+
+#if FAST2D_PART == 0
+namespace {
+
 // the variant table: lengths up to 4096 in steps of 32
 std::atomic<int> g_row_var[129], g_col_var[129];
 int slot(int len) { return (len % 32 == 0 && len >= 32 && len <= 4096) ? len / 32 : 0; }
+
+// the first part that holds the variant serves the launch
+template <int PART = 0, typename F>
+hipError_t any_part(F f) {
+    if constexpr (PART < kParts) {
+        const hipError_t e = f(Fast2dPart<PART>{});
+        return e == hipErrorInvalidValue ? any_part<PART + 1>(f) : e;
+    } else {
+        return hipErrorInvalidValue;
+    }
+}
 
 }  // namespace
 
@@ -1359,6 +1407,8 @@ bool fast2d_col_ok(int L, int split, int var) {
 #undef CASE
     return false;
 }
+
+#endif  // part 0
 
 // the fast row kernels of one compiled variant: periodic x (XPER) or
 // zero-padded, packed 2D (NAT false) or natural 3D (NAT true) spectrum
@@ -1432,39 +1482,27 @@ hipError_t launch_row_inv_v(const Grid& g, const Phys& p, const float2* twx, flo
     }
 }
 
-// 2D (nz = 1): the packed, tiled spectrum of the column kernel; 3D: the
-// natural layout [c][row][nkxp] of the 3D column passes
-hipError_t launch_row_fwd_fast(const Grid& g, const float2* twx, float2* S, const FwdArgs& fa,
-                               DevState* st, hipStream_t s) {
-    if (g.nx > g.Px || g.nkxp < g.Px / 2 || g.tsh < 0 || (g.Px / 2) % (1 << g.tsh)) return hipErrorInvalidValue;
-    const bool nat = g.nz > 1;
-    if (nat && (g.nkxp < g.Px / 2 + 1 || g.nkx != g.Px / 2 + 1)) return hipErrorInvalidValue;
-    const int var = g.rvar;
+#define PART_MEMBER template <> hipError_t Fast2dPart<FAST2D_PART>
+
+PART_MEMBER::row_fwd(const Grid& g, const float2* twx, float2* S, const FwdArgs& fa, DevState* st, hipStream_t s,
+                     bool nat) {
 #define CASE(PX, E, NQ, V) \
-    if (g.Px == PX && var == V) return launch_row_fwd_v<PX, E, NQ>(g, twx, S, fa, st, s, nat);
-    ROW_VARIANTS(CASE)
+    if (g.Px == PX && g.rvar == V) return launch_row_fwd_v<PX, E, NQ>(g, twx, S, fa, st, s, nat);
+    PART_ROW_VARIANTS(CASE)
 #undef CASE
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_row_inv_fast(const Grid& g, const Phys& p, const float2* twx, float2* S,
-                               const StageArgs& sa, DevState* st, hipStream_t s) {
-    if (g.nx > g.Px || g.nkxp < g.Px / 2 || sa.nk > kMaxK || g.tsh < 0 || (g.Px / 2) % (1 << g.tsh))
-        return hipErrorInvalidValue;
-    if ((sa.mode == ROW_STAGE || sa.mode == ROW_ERROR) && sa.nk < 1) return hipErrorInvalidValue;
-    const bool nat = g.nz > 1;
-    if (nat && (g.nkxp < g.Px / 2 + 1 || g.nkx != g.Px / 2 + 1)) return hipErrorInvalidValue;
-    const int var = g.rvar;
+PART_MEMBER::row_inv(const Grid& g, const Phys& p, const float2* twx, float2* S, const StageArgs& sa, DevState* st,
+                     hipStream_t s, bool nat) {
 #define CASE(PX, E, NQ, V) \
-    if (g.Px == PX && var == V) return launch_row_inv_v<PX, E, NQ>(g, p, twx, S, sa, st, s, nat);
-    ROW_VARIANTS(CASE)
+    if (g.Px == PX && g.rvar == V) return launch_row_inv_v<PX, E, NQ>(g, p, twx, S, sa, st, s, nat);
+    PART_ROW_VARIANTS(CASE)
 #undef CASE
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_col2d_fast(const Col2dArgs& a, DevState* st, hipStream_t s) {
-    if (a.Py % 2 || a.ny > a.Py / 2 || a.nkx_full != a.nkx + 1 || a.nkx % 2) return hipErrorInvalidValue;
-    if (a.tsh < 0 || a.nkx % (1 << a.tsh) || (a.nq != 2 && a.nq != 4) || a.nkx % a.nq) return hipErrorInvalidValue;
+PART_MEMBER::col(const Col2dArgs& a, DevState* st, hipStream_t s) {
     const int L = a.Py / 2;
     const int var = a.var;
 #define CASE(LL, E, NQ, V)                                                                \
@@ -1476,9 +1514,81 @@ hipError_t launch_col2d_fast(const Col2dArgs& a, DevState* st, hipStream_t s) {
         hot_launch(col2d_fast<LL, E, NQ>, dim3(CF::blocks(a.nkx)), dim3(CF::NT), CF::bytes(), s, a, st); \
         return hipGetLastError();                                                         \
     }
-    COL_VARIANTS(CASE)
+    PART_COL_VARIANTS(CASE)
 #undef CASE
     return hipErrorInvalidValue;
+}
+
+PART_MEMBER::row_fwd_group(int Px, int var, const FilmRow* films, const int2* map, int nblocks, hipStream_t s) {
+#define CASE(PX, E, NQ, V)                                                                \
+    if (Px == PX && var == V) {                                                           \
+        using R_ = RowSplit<PX, E, NQ>;                                                   \
+        constexpr int lds = R_::template fwd_bytes<false>();                              \
+        hipError_t e_ = allow_lds(reinterpret_cast<const void*>(&llg::row_fwd_group<PX, E, NQ>), lds); \
+        if (e_ != hipSuccess) return e_;                                                  \
+        hipLaunchKernelGGL((llg::row_fwd_group<PX, E, NQ>), dim3(nblocks), dim3(R_::NT), lds, s, films, map); \
+        return hipGetLastError();                                                         \
+    }
+    PART_ROW_VARIANTS(CASE)
+#undef CASE
+    return hipErrorInvalidValue;
+}
+
+PART_MEMBER::row_inv_group(int Px, int var, const FilmRow* films, const int2* map, int nblocks, hipStream_t s) {
+#define CASE(PX, E, NQ, V)                                                                \
+    if (Px == PX && var == V) {                                                           \
+        using R_ = RowSplit<PX, E, NQ>;                                                   \
+        constexpr int lds = R_::template inv_bytes<false>();                              \
+        hipError_t e_ = allow_lds(reinterpret_cast<const void*>(&llg::row_inv_group<PX, E, NQ>), lds); \
+        if (e_ != hipSuccess) return e_;                                                  \
+        hipLaunchKernelGGL((llg::row_inv_group<PX, E, NQ>), dim3(nblocks), dim3(R_::NT), lds, s, films, map); \
+        return hipGetLastError();                                                         \
+    }
+    PART_ROW_VARIANTS(CASE)
+#undef CASE
+    return hipErrorInvalidValue;
+}
+
+PART_MEMBER::col_group(int L, int var, const FilmCol* films, const int2* map, int nblocks, hipStream_t s) {
+#define CASE(LL, E, NQ, V)                                                                \
+    if (L == LL && var == V) {                                                            \
+        using CF = ColSplit<LL, E, NQ>;                                                   \
+        constexpr int lds = CF::bytes();                                                  \
+        hipError_t e_ = allow_lds(reinterpret_cast<const void*>(&llg::col_group<LL, E, NQ>), lds); \
+        if (e_ != hipSuccess) return e_;                                                  \
+        hipLaunchKernelGGL((llg::col_group<LL, E, NQ>), dim3(nblocks), dim3(CF::NT), lds, s, films, map); \
+        return hipGetLastError();                                                         \
+    }
+    PART_COL_VARIANTS(CASE)
+#undef CASE
+    return hipErrorInvalidValue;
+}
+
+#if FAST2D_PART == 0
+// 2D (nz = 1): the packed, tiled spectrum of the column kernel; 3D: the
+// natural layout [c][row][nkxp] of the 3D column passes
+hipError_t launch_row_fwd_fast(const Grid& g, const float2* twx, float2* S, const FwdArgs& fa,
+                               DevState* st, hipStream_t s) {
+    if (g.nx > g.Px || g.nkxp < g.Px / 2 || g.tsh < 0 || (g.Px / 2) % (1 << g.tsh)) return hipErrorInvalidValue;
+    const bool nat = g.nz > 1;
+    if (nat && (g.nkxp < g.Px / 2 + 1 || g.nkx != g.Px / 2 + 1)) return hipErrorInvalidValue;
+    return any_part([&](auto part) { return part.row_fwd(g, twx, S, fa, st, s, nat); });
+}
+
+hipError_t launch_row_inv_fast(const Grid& g, const Phys& p, const float2* twx, float2* S,
+                               const StageArgs& sa, DevState* st, hipStream_t s) {
+    if (g.nx > g.Px || g.nkxp < g.Px / 2 || sa.nk > kMaxK || g.tsh < 0 || (g.Px / 2) % (1 << g.tsh))
+        return hipErrorInvalidValue;
+    if ((sa.mode == ROW_STAGE || sa.mode == ROW_ERROR) && sa.nk < 1) return hipErrorInvalidValue;
+    const bool nat = g.nz > 1;
+    if (nat && (g.nkxp < g.Px / 2 + 1 || g.nkx != g.Px / 2 + 1)) return hipErrorInvalidValue;
+    return any_part([&](auto part) { return part.row_inv(g, p, twx, S, sa, st, s, nat); });
+}
+
+hipError_t launch_col2d_fast(const Col2dArgs& a, DevState* st, hipStream_t s) {
+    if (a.Py % 2 || a.ny > a.Py / 2 || a.nkx_full != a.nkx + 1 || a.nkx % 2) return hipErrorInvalidValue;
+    if (a.tsh < 0 || a.nkx % (1 << a.tsh) || (a.nq != 2 && a.nq != 4) || a.nkx % a.nq) return hipErrorInvalidValue;
+    return any_part([&](auto part) { return part.col(a, st, s); });
 }
 
 // ---- grouped launchers ------------------------------------------------------------
@@ -1544,49 +1654,14 @@ int fast2d_col_width(int L, int var) {
 
 hipError_t launch_row_fwd_group(int Px, int var, const FilmRow* films, const int2* map, int nblocks,
                                 hipStream_t s) {
-#define CASE(PX, E, NQ, V)                                                                \
-    if (Px == PX && var == V) {                                                           \
-        using R_ = RowSplit<PX, E, NQ>;                                                   \
-        constexpr int lds = R_::template fwd_bytes<false>();                              \
-        hipError_t e_ = allow_lds(reinterpret_cast<const void*>(&row_fwd_group<PX, E, NQ>), lds); \
-        if (e_ != hipSuccess) return e_;                                                  \
-        hipLaunchKernelGGL((row_fwd_group<PX, E, NQ>), dim3(nblocks), dim3(R_::NT), lds, s, films, map); \
-        return hipGetLastError();                                                         \
-    }
-    ROW_VARIANTS(CASE)
-#undef CASE
-    return hipErrorInvalidValue;
+    return any_part([&](auto part) { return part.row_fwd_group(Px, var, films, map, nblocks, s); });
 }
-
 hipError_t launch_row_inv_group(int Px, int var, const FilmRow* films, const int2* map, int nblocks,
                                 hipStream_t s) {
-#define CASE(PX, E, NQ, V)                                                                \
-    if (Px == PX && var == V) {                                                           \
-        using R_ = RowSplit<PX, E, NQ>;                                                   \
-        constexpr int lds = R_::template inv_bytes<false>();                              \
-        hipError_t e_ = allow_lds(reinterpret_cast<const void*>(&row_inv_group<PX, E, NQ>), lds); \
-        if (e_ != hipSuccess) return e_;                                                  \
-        hipLaunchKernelGGL((row_inv_group<PX, E, NQ>), dim3(nblocks), dim3(R_::NT), lds, s, films, map); \
-        return hipGetLastError();                                                         \
-    }
-    ROW_VARIANTS(CASE)
-#undef CASE
-    return hipErrorInvalidValue;
+    return any_part([&](auto part) { return part.row_inv_group(Px, var, films, map, nblocks, s); });
 }
-
 hipError_t launch_col_group(int L, int var, const FilmCol* films, const int2* map, int nblocks, hipStream_t s) {
-#define CASE(LL, E, NQ, V)                                                                \
-    if (L == LL && var == V) {                                                            \
-        using CF = ColSplit<LL, E, NQ>;                                                   \
-        constexpr int lds = CF::bytes();                                                  \
-        hipError_t e_ = allow_lds(reinterpret_cast<const void*>(&col_group<LL, E, NQ>), lds); \
-        if (e_ != hipSuccess) return e_;                                                  \
-        hipLaunchKernelGGL((col_group<LL, E, NQ>), dim3(nblocks), dim3(CF::NT), lds, s, films, map); \
-        return hipGetLastError();                                                         \
-    }
-    COL_VARIANTS(CASE)
-#undef CASE
-    return hipErrorInvalidValue;
+    return any_part([&](auto part) { return part.col_group(L, var, films, map, nblocks, s); });
 }
 
 // sizes beyond the hardware are refused before any runtime call; a failed
@@ -1615,5 +1690,7 @@ hipError_t raise_lds_limit(const void* fn, int bytes) {
     if (v < bytes) v = bytes;
     return hipSuccess;
 }
+
+#endif  // part 0
 
 }  // namespace llg

@@ -126,6 +126,7 @@ struct llg_solver {
     float2 *twx = nullptr, *twy = nullptr, *twz = nullptr;
     int wy = 1, wz = 1;       // column tile widths
     bool fast2d = false;      // 2D with compiled FFT lengths: packed spectrum kernels
+    bool tunable = false;     // fast2d at the shortest padded lengths: the tuning calls serve it
     bool fastrows = false;    // row passes of compiled length (2D packed or 3D natural layout)
     bool fast3dy = false;     // 3D, y axis of compiled length: tiled y passes
     bool fast3dz = false;     // 3D, z axis of compiled length: tiled z pass
@@ -213,6 +214,41 @@ int col_width(int Lh, int n) {
 }
 
 bool two_d(const llg_solver* s) { return s->nz == 1; }
+
+int spectrum_stride(int Px) { return (Px / 2 + 1 + 15) / 16 * 16; }
+
+// scratch of the no-allocation evaluation for FFT lengths P
+size_t noalloc_need(const int n[3], const int P[3]) {
+    const size_t row = sizeof(float2) * 3 * (size_t)spectrum_stride(P[0]);
+    const size_t sy = n[2] > 1 ? row * (size_t)n[2] * P[1] : 0;
+    return kNoAllocStateBytes + (row * (size_t)n[1] * n[2] + 255) / 256 * 256 + sy;
+}
+
+// Lengthens the open axes' FFT lengths P (the shortest 2-3-5-7 lengths >=
+// 2n) to the next lengths with compiled kernels where every pass then runs
+// compiled: zero padding beyond 2n - 1 leaves the convolution unchanged
+// (Sec. 3.2).  RK4 at 250 x 63 cells: 61 us per evaluation with the
+// runtime-length kernels at 500 x 126 points, 18 with the compiled ones at
+// 512 x 128; at 1000 x 600 cells 322 (2000 x 1200 points) against 87 (2048 x
+// 1536); one evaluation of 100 x 37 cells 56 against 30.  The compiled
+// lengths are at most 3/2 apart, so the longer padding never costs what the
+// compiled kernels gain (3.3 to 3.7).  Kept as they are: a geometry whose
+// spectrum would outgrow the scratch of the no-allocation evaluation only
+// by the longer padding.
+void compiled_lengths(const int n[3], const int pb[3], int P[3]) {
+    int Q[3] = {P[0], P[1], P[2]};
+    if (n[2] == 1) {
+        if (pb[1]) return;
+        const int px = pb[0] ? (fast2d_row_ok(P[0], 0, true) ? P[0] : 0) : fast2d_row_len_at_least(P[0]);
+        const int l = fast2d_col_len_at_least(P[1] / 2);
+        if (px == 0 || l == 0 || (px > 2048 && px != P[0])) return;
+        if (!fast2d_row_ok(px, 0, pb[0] != 0) || !fast2d_col_ok(l, 1, 0) || (px / 2) % fast2d_col_width(l, 0)) return;
+        Q[0] = px;
+        Q[1] = 2 * l;
+    }
+    if (noalloc_need(n, P) <= kNoAllocBytes && noalloc_need(n, Q) > kNoAllocBytes) return;
+    for (int a = 0; a < 3; ++a) P[a] = Q[a];
+}
 
 Phys make_phys(const llg_solver* s, double dt_thermal) {
     Material m;
@@ -766,11 +802,20 @@ llg_status llg_set_geometry(llg_solver* s, int nx, int ny, int nz, int pbc_x, in
     }
     if (nz == 1) P[2] = 1;
     const int split_y = !pb[1], split_z = nz > 1 && !pb[2];
-    const int Ly = split_y ? P[1] / 2 : P[1];
+    int Ly = split_y ? P[1] / 2 : P[1];
     const int Lz = split_z ? P[2] / 2 : P[2];
     if (P[0] > kMaxPx || Ly > kMaxHalf || Lz > kMaxHalf)
         return fail(s, LLG_E_UNSUPPORTED, "FFT lengths %d x %d x %d exceed this build's limits", P[0], P[1], P[2]);
     if (P[0] % 2) return fail(s, LLG_E_UNSUPPORTED, "x FFT length must be even (periodic nx odd)");
+    const int P0[3] = {P[0], P[1], P[2]};   // the shortest lengths
+    // LLG_FORCE_GENERIC=1 selects the runtime-length kernels everywhere (used
+    // by the tests to check both implementations against the oracle)
+    const char* gen = getenv("LLG_FORCE_GENERIC");
+    const bool generic = gen && gen[0] == '1';
+    if (!generic) {
+        compiled_lengths(n, pb, P);
+        Ly = split_y ? P[1] / 2 : P[1];
+    }
     (void)hipStreamSynchronize(s->stream);
     free_buffers(s);
     s->have_geom = false;
@@ -786,7 +831,7 @@ llg_status llg_set_geometry(llg_solver* s, int nx, int ny, int nz, int pbc_x, in
     for (int a = 0; a < 3; ++a) g.pbc[a] = pb[a];
     g.Px = P[0]; g.Py = P[1]; g.Pz = P[2];
     g.nkx = P[0] / 2 + 1;
-    g.nkxp = (g.nkx + 15) / 16 * 16;
+    g.nkxp = spectrum_stride(P[0]);
     g.tsh = fast2d_tile_shift();
     g.split_y = split_y;
     g.split_z = split_z;
@@ -795,9 +840,6 @@ llg_status llg_set_geometry(llg_solver* s, int nx, int ny, int nz, int pbc_x, in
     s->wy = col_width(Ly, ny);
     s->wz = col_width(Lz, nz);
     if (s->wy < 1 || s->wz < 1) return fail(s, LLG_E_UNSUPPORTED, "column pass does not fit");
-    // LLG_FORCE_GENERIC=1 selects the runtime-length kernels everywhere (used
-    // by the tests to check both implementations against the oracle)
-    const char* gen = getenv("LLG_FORCE_GENERIC");
     // compiled variants: the table's defaults where they serve this geometry
     // (else variant 0); kept by this solver until its own llg_autotune or
     // llg_set_variants, whatever later calls do to the table
@@ -806,11 +848,12 @@ llg_status llg_set_geometry(llg_solver* s, int nx, int ny, int nz, int pbc_x, in
     g.cvar = fast2d_col_variant(Ly);
     if (!fast2d_col_ok(Ly, split_y, g.cvar) || (P[0] / 2) % fast2d_col_width(Ly, g.cvar)) g.cvar = 0;
     s->fast2d = nz == 1 && fast2d_row_ok(P[0], g.rvar, nx == P[0]) && fast2d_col_ok(Ly, split_y, g.cvar) &&
-                ny <= Ly && (P[0] / 2) % fast2d_col_width(Ly, g.cvar) == 0 && !(gen && gen[0] == '1');
+                ny <= Ly && (P[0] / 2) % fast2d_col_width(Ly, g.cvar) == 0 && !generic;
+    s->tunable = s->fast2d && P[0] == P0[0] && P[1] == P0[1];
     s->fastrows = s->fast2d || (nz > 1 && fast2d_row_ok(P[0], g.rvar, nx == P[0]) && (nx == P[0] || 2 * nx <= P[0]) &&
-                                !(gen && gen[0] == '1'));
-    s->fast3dy = nz > 1 && fast3d_col_ok(P[1], split_y, false) && ny <= Ly && !(gen && gen[0] == '1');
-    s->fast3dz = nz > 1 && fast3d_col_ok(P[2], split_z, true) && nz <= Lz && !(gen && gen[0] == '1');
+                                !generic);
+    s->fast3dy = nz > 1 && fast3d_col_ok(P[1], split_y, false) && ny <= Ly && !generic;
+    s->fast3dz = nz > 1 && fast3d_col_ok(P[2], split_z, true) && nz <= Lz && !generic;
     // x transforms above 2048 points exist only as compiled 2D row kernels
     // (the runtime-length kernels stop at 2048)
     if (P[0] > 2048 && !(s->fast2d && nz == 1))
@@ -1011,8 +1054,8 @@ llg_status llg_eval_heff_noalloc(llg_solver* s, const float* m_dev, float* h_dev
                                     "call llg_eval_heff, llg_step or llg_run once first");
     const Grid& g = s->g;
     const size_t sbytes = (sizeof(float2) * 3 * (size_t)g.nrows * g.nkxp + 255) / 256 * 256;
-    const size_t sybytes = two_d(s) ? 0 : sizeof(float2) * 3 * (size_t)g.nz * g.Py * g.nkxp;
-    const size_t need = kNoAllocStateBytes + sbytes + sybytes;
+    const int ng[3] = {g.nx, g.ny, g.nz}, Pg[3] = {g.Px, g.Py, g.Pz};
+    const size_t need = noalloc_need(ng, Pg);
     if (need > kNoAllocBytes)
         return fail(s, LLG_E_UNSUPPORTED, "this geometry needs %zu bytes of scratch, above the %zu-byte "
                                           "static array of the no-allocation evaluation", need, kNoAllocBytes);
@@ -1364,7 +1407,7 @@ llg_status llg_autotune(llg_solver* s, int iters, double* ms_out, int n_out, int
     if (iters < 1) return fail(s, LLG_E_ARG, "iters must be >= 1");
     if ((rc = ready(s, true)) != LLG_OK) return rc;
     if ((rc = ensure_kernel(s)) != LLG_OK) return rc;
-    if (!s->fast2d) return fail(s, LLG_E_UNSUPPORTED, "no compiled variants for this geometry");
+    if (!s->tunable) return fail(s, LLG_E_UNSUPPORTED, "no compiled variants for this geometry");
     const Phys p = make_phys(s, s->last_dt);
     if (!p.demag_on) return fail(s, LLG_E_STATE, "tuning needs the demag term");
     int was = 0;
@@ -1436,7 +1479,7 @@ llg_status llg_autotune_attempts(llg_solver* s, double max_err, double dt0, int 
         return fail(s, LLG_E_ARG, "need attempts >= 1, max_err > 0, dt0 >= 0");
     if ((rc = ready(s, true)) != LLG_OK) return rc;
     if ((rc = ensure_kernel(s)) != LLG_OK) return rc;
-    if (!s->fast2d) return fail(s, LLG_E_UNSUPPORTED, "no compiled variants for this geometry");
+    if (!s->tunable) return fail(s, LLG_E_UNSUPPORTED, "no compiled variants for this geometry");
     const Phys p = make_phys(s, 0.0);
     if (!p.demag_on) return fail(s, LLG_E_STATE, "tuning needs the demag term");
     DevState h0;
@@ -1518,7 +1561,7 @@ llg_status llg_autotune_attempts(llg_solver* s, double max_err, double dt0, int 
 llg_status llg_set_variants(llg_solver* s, int row_var, int col_var) {
     llg_status rc = enter(s);
     if (rc != LLG_OK) return rc;
-    if (!s->fast2d) return fail(s, LLG_E_UNSUPPORTED, "no compiled variants for this geometry");
+    if (!s->tunable) return fail(s, LLG_E_UNSUPPORTED, "no compiled variants for this geometry");
     const int Px = s->g.Px, L = s->g.Py / 2;
     if (!fast2d_row_ok(Px, row_var, s->g.nx == Px) || !fast2d_col_ok(L, 1, col_var) ||
         (Px / 2) % fast2d_col_width(L, col_var))
@@ -1539,7 +1582,7 @@ llg_status llg_variant_shape(int kind, int length, int variant, int* elems, int*
 llg_status llg_get_variants(llg_solver* s, int* row_var, int* col_var) {
     if (!s || !row_var || !col_var) return LLG_E_ARG;
     if (!s->have_geom) return fail(s, LLG_E_STATE, "geometry not set");
-    if (!s->fast2d) return fail(s, LLG_E_UNSUPPORTED, "no compiled variants for this geometry");
+    if (!s->tunable) return fail(s, LLG_E_UNSUPPORTED, "no compiled variants for this geometry");
     *row_var = s->g.rvar;
     *col_var = s->g.cvar;
     return LLG_OK;
