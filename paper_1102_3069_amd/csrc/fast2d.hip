@@ -265,7 +265,10 @@ __device__ __forceinline__ void row_fwd_body(const Grid& g, const float2* __rest
     float2* tws = (float2*)(lds + R::O_TWS);
     float2* scr = (float2*)(lds + R::O_SCR);
     float* nm = (float*)(lds + R::O_M);
-    if (st->done) return;
+    constexpr bool EARLY = R::BIG || NAT;
+    const StateRead<!EARLY> sr(st);
+    if (EARLY || gridDim.x >= kManyBlocks)
+        if (st->done) return;
     const int tid = threadIdx.x;
     const int gi = R::P == 64 ? __builtin_amdgcn_readfirstlane(tid / R::P) : tid / R::P;
     const int lg = tid % R::P;
@@ -279,8 +282,9 @@ __device__ __forceinline__ void row_fwd_body(const Grid& g, const float2* __rest
     twc.load(twx, tid);
     typename R::F::template TwFill<NT> twf;
     twf.load(twx, tid);
-    const int cur = st->cur;
-    const float c1 = st->dtau * fa.a1;
+    if constexpr (!EARLY) __builtin_amdgcn_sched_barrier(0);
+    const int cur = sr.cur(), done = EARLY ? 0 : sr.done();
+    const float c1 = sr.dtau() * fa.a1;
     const int cs = g.ncells;
     const float* mi = resolve(fa.m_in, cur);
     const float* m0 = resolve(fa.m0, cur);
@@ -289,22 +293,9 @@ __device__ __forceinline__ void row_fwd_body(const Grid& g, const float2* __rest
     const int nx = g.nx;
     const float rnx = 1.0f / (float)nx;
     const int nrow = min(2 * R::RP, g.nrows - rb);
-    // one cell: the stage state (m0 + c1 k1, normalised) or m itself
-    auto cell = [&](int qq, float& ax, float& ay, float& az) {
-        if (fa.combine) {
-            ax = m0[qq] + c1 * k1[qq];
-            ay = m0[cs + qq] + c1 * k1[cs + qq];
-            az = m0[2 * cs + qq] + c1 * k1[2 * cs + qq];
-            const float inv = rsqrtf(ax * ax + ay * ay + az * az);
-            ax *= inv; ay *= inv; az *= inv;
-        } else {
-            ax = mi[qq]; ay = mi[cs + qq]; az = mi[2 * cs + qq];
-        }
-    };
     if ((nx & 3) == 0 && (cs & 3) == 0) {
         // four consecutive cells per thread, 16-byte loads and stores (rows
-        // and components start 16-byte aligned); the same arithmetic per
-        // cell as `cell`
+        // and components start 16-byte aligned)
         const int n4 = nx >> 2;
         auto ld4 = [](const float* p, float (&o)[4]) {
             const float4 w = *reinterpret_cast<const float4*>(p);
@@ -341,24 +332,49 @@ __device__ __forceinline__ void row_fwd_body(const Grid& g, const float2* __rest
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 const float4 w = make_float4(v[c][0], v[c][1], v[c][2], v[c][3]);
-                if (fa.combine) *reinterpret_cast<float4*>(mo + c * cs + qq) = w;
+                if (fa.combine && !done) *reinterpret_cast<float4*>(mo + c * cs + qq) = w;
                 *reinterpret_cast<float4*>(row + c * NXM + x) = w;
             }
         }
     } else {
-        for (int e = tid; e < nrow * nx; e += NT) {
-            int ri, x;
-            split_cell(e, nx, rnx, ri, x);
-            const int qq = (rb + ri) * nx + x;
-            float ax, ay, az;
-            cell(qq, ax, ay, az);
-            if (fa.combine) { mo[qq] = ax; mo[cs + qq] = ay; mo[2 * cs + qq] = az; }
-            float* row = nm + ri * 3 * NXM;
-            row[x] = ax; row[NXM + x] = ay; row[2 * NXM + x] = az;
+        // one cell at a time, up to four cells' reads in flight
+        constexpr int MAXIT = (2 * R::RP * NXM + NT - 1) / NT, CC = MAXIT < 4 ? MAXIT : 4;
+        for (int i0 = 0; i0 < MAXIT; i0 += CC) {
+            float v[CC][3], k[CC][3];
+            int ri[CC], x[CC];
+#pragma unroll
+            for (int ii = 0; ii < CC; ++ii) {
+                const int e = tid + (i0 + ii) * NT;
+                ri[ii] = -1;
+                if (i0 + ii >= MAXIT || e >= nrow * nx) continue;
+                split_cell(e, nx, rnx, ri[ii], x[ii]);
+                const int qq = (rb + ri[ii]) * nx + x[ii];
+                const float* src = fa.combine ? m0 : mi;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    v[ii][c] = src[c * cs + qq];
+                    if (fa.combine) k[ii][c] = k1[c * cs + qq];
+                }
+            }
+#pragma unroll
+            for (int ii = 0; ii < CC; ++ii) {
+                if (ri[ii] < 0) continue;
+                float ax = v[ii][0], ay = v[ii][1], az = v[ii][2];
+                if (fa.combine) {
+                    const int qq = (rb + ri[ii]) * nx + x[ii];
+                    ax += c1 * k[ii][0]; ay += c1 * k[ii][1]; az += c1 * k[ii][2];
+                    const float inv = rsqrtf(ax * ax + ay * ay + az * az);
+                    ax *= inv; ay *= inv; az *= inv;
+                    if (!done) { mo[qq] = ax; mo[cs + qq] = ay; mo[2 * cs + qq] = az; }
+                }
+                float* row = nm + ri[ii] * 3 * NXM + x[ii];
+                row[0] = ax; row[NXM] = ay; row[2 * NXM] = az;
+            }
         }
     }
     twc.store(tw, tid);
     twf.store(tws, tid);
+    if (!EARLY && done) return;
     __syncthreads();
     R::template forward<NXM, NAT>(g, S, scr, tw, tws, nm, kind, q, pair, lg, gbase, rb);
 }
@@ -368,7 +384,8 @@ __global__ __launch_bounds__((RowSplit<PX, E2, NQ>::NT)) void row_fwd_fast(Grid 
                                                             float2* __restrict__ S, FwdArgs fa,
                                                             DevState* __restrict__ st) {
     extern __shared__ char dyn_lds[];
-    row_fwd_body<PX, E2, NQ, XPER, NAT>(g, twx, S, fa, st, xcd_remap_blocks(blockIdx.x, gridDim.x), dyn_lds);
+    const int b = touch_args<sizeof(Grid) + 16 + sizeof(FwdArgs)>(blockIdx.x);
+    row_fwd_body<PX, E2, NQ, XPER, NAT>(g, twx, S, fa, st, xcd_remap_blocks(b, gridDim.x), dyn_lds);
 }
 
 // exchange + anisotropy + applied + thermal field of cell x of a row whose
@@ -468,7 +485,10 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
     float* mrow = (float*)(lds + R::O_MI);
     float* nm = (float*)(lds + R::template o_nm<XPER>());   // aliases mrow
     float* wmax = (float*)(lds + R::template o_wmax<XPER>());
-    if (st->done) return;
+    constexpr bool EARLY = BIG || NAT;
+    const StateRead<!EARLY> sr(st);
+    if (EARLY || gridDim.x >= kManyBlocks)
+        if (st->done) return;
     const int tid = threadIdx.x;
     // a group that fills its wavefront: the group index is wave-uniform
     const int gi = P == 64 ? __builtin_amdgcn_readfirstlane(tid / P) : tid / P;
@@ -479,10 +499,8 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
     const int rb = row_block_start<NAT>(g, blk, 2 * RP);   // first row of the block
     const int r0 = rb + 2 * pair;
     const bool v0 = r0 < g.nrows, v1 = r0 + 1 < g.nrows;
-    const int cur = st->cur;
-    const float dtau = st->dtau;
-    const uint64_t step = (uint64_t)st->step;
     const int nx = g.nx, ny = g.ny;
+    const float rnx = 1.0f / (float)nx;
     // (y, z) of the block's row rb + ri: one division per block, then steps
     const int y0 = rb % ny, z0 = rb / ny;
     auto plane_of = [&](int ri, int& y, int& z) {
@@ -491,10 +509,6 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
         while (y >= ny) { y -= ny; ++z; }
     };
     const int cs = g.ncells;
-    const float* mi = resolve(sa.m_in, cur);
-    const float* m0 = resolve(sa.m0, cur);
-    float* mo = resolve(sa.m_out, cur);
-    float* ko = resolve(sa.k_out, cur);
     const bool stage = sa.mode == ROW_STAGE;
     const bool errm = sa.mode == ROW_ERROR || ((stage || sa.mode == ROW_KONLY) && sa.with_err);
 
@@ -508,39 +522,6 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
     twc.load(twx, tid);
     typename F::template TwFill<NT> twf;
     twf.load(twx, tid);
-    // staged row rq holds grid row rb - 1 + rq; NAT (3D): the halo rows serve
-    // only as in-plane neighbours, the periodic y wrap and the z neighbours
-    // come from global memory
-    auto staged_row = [&](int rq, bool& ok) {
-        int row = rb - 1 + rq;
-        ok = row >= 0 && row < g.nrows;
-        if (!NAT && g.pbc[1]) { row = row < 0 ? row + ny : (row >= ny ? row - ny : row); ok = true; }
-        return row;
-    };
-    // 16-byte loads where every (row, component) run of nx floats starts
-    // 16-byte aligned; BIG: no staged rows (the per-cell work reads m from
-    // global memory)
-    const bool vec4 = !BIG && (nx & 3) == 0 && (cs & 3) == 0;
-    const int n4 = nx >> 2;
-    constexpr int ITR = BIG ? 1 : (R::NR * 3 * (NXM / 4) + NT - 1) / NT;
-    constexpr bool ROW1 = ITR <= 8;   // the staged rows in the first round
-    auto row_load = [&](int t, float4& v, int& d) {
-        d = -1;
-        if (t >= R::NR * 3 * n4) return;
-        const int rq = t / (3 * n4), rem = t - rq * 3 * n4;
-        const int c = rem / n4, x4 = rem - c * n4;
-        bool ok;
-        const int row = staged_row(rq, ok);
-        v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (ok) v = *reinterpret_cast<const float4*>(mi + (size_t)c * cs + (size_t)row * nx + 4 * x4);
-        d = rq * 3 * NXM + c * NXM + 4 * x4;
-    };
-    float4 rv[ROW1 ? ITR : 1];
-    int rd[ROW1 ? ITR : 1];
-    if (ROW1 && vec4) {
-#pragma unroll
-        for (int it = 0; it < (ROW1 ? ITR : 1); ++it) row_load(tid + it * NT, rv[it], rd[it]);
-    }
     // X[k], k = NQ j + q, from the stored columns kx < PX/2 and the
     // Hermitian symmetry X[PX - k] = conj X[k] of a real row (class
     // (NQ - q) mod NQ, index LQ - j for q = 0, LQ - 1 - j otherwise): the
@@ -592,6 +573,82 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
         }
     };
     if (p.demag_on) spec_load(0);
+    // the reads that depend on the device state, whose own read is on its
+    // way since the start, go last
+    if constexpr (!EARLY) __builtin_amdgcn_sched_barrier(0);
+    const int cur = sr.cur();
+    const float dtau = sr.dtau();
+    const float* mi = resolve(sa.m_in, cur);
+    const float* m0 = resolve(sa.m0, cur);
+    float* mo = resolve(sa.m_out, cur);
+    float* ko = resolve(sa.k_out, cur);
+    // staged row rq holds grid row rb - 1 + rq; NAT (3D): the halo rows serve
+    // only as in-plane neighbours, the periodic y wrap and the z neighbours
+    // come from global memory
+    auto staged_row = [&](int rq, bool& ok) {
+        int row = rb - 1 + rq;
+        ok = row >= 0 && row < g.nrows;
+        if (!NAT && g.pbc[1]) { row = row < 0 ? row + ny : (row >= ny ? row - ny : row); ok = true; }
+        return row;
+    };
+    // 16-byte loads where every (row, component) run of nx floats starts
+    // 16-byte aligned, else single values, into the same registers; BIG: no
+    // staged rows (the per-cell work reads m from global memory)
+    const bool vec4 = !BIG && (nx & 3) == 0 && (cs & 3) == 0;
+    constexpr int ITR = BIG ? 1 : (R::NR * 3 * (NXM / 4) + NT - 1) / NT;
+    constexpr bool ROW1 = ITR <= 8;   // the staged rows in the first round
+    const int nu = vec4 ? nx >> 2 : nx;          // units of a row
+    const float rnu = 1.0f / (float)nu;
+    // unit t of the staged rows: row and component rc = 3 rq + c, place xu
+    auto row_unit = [&](int t, int& rc, int& xu) {
+        if (BIG || t >= R::NR * 3 * nu) return false;
+        split_cell(t, nu, rnu, rc, xu);
+        return true;
+    };
+    auto row_src = [&](int rc, bool& ok) {
+        const int rq = rc / 3, c = rc - 3 * rq;
+        return mi + (size_t)c * cs + (size_t)staged_row(rq, ok) * nx;
+    };
+    constexpr int CR = ROW1 ? ITR : 8;           // 16-byte units per round
+    float rv[4 * CR];
+    auto rows_load = [&](int i0) {
+        int rc, xu;
+        bool ok;
+#pragma unroll
+        for (int ii = 0; ii < 4 * CR; ++ii) rv[ii] = 0.f;
+        if (vec4) {
+#pragma unroll
+            for (int ii = 0; ii < CR; ++ii) {
+                if (i0 + ii >= ITR || !row_unit(tid + (i0 + ii) * NT, rc, xu)) continue;
+                const float* src = row_src(rc, ok);
+                if (!ok) continue;
+                const float4 v = *reinterpret_cast<const float4*>(src + 4 * xu);
+                rv[4 * ii] = v.x; rv[4 * ii + 1] = v.y; rv[4 * ii + 2] = v.z; rv[4 * ii + 3] = v.w;
+            }
+        } else {
+#pragma unroll
+            for (int ii = 0; ii < 4 * CR; ++ii) {
+                if (!row_unit(tid + (4 * i0 + ii) * NT, rc, xu)) continue;
+                const float* src = row_src(rc, ok);
+                if (ok) rv[ii] = src[xu];
+            }
+        }
+    };
+    auto rows_store = [&](int i0) {
+        int rc, xu;
+        if (vec4) {
+#pragma unroll
+            for (int ii = 0; ii < CR; ++ii)
+                if (i0 + ii < ITR && row_unit(tid + (i0 + ii) * NT, rc, xu))
+                    *reinterpret_cast<float4*>(mrow + rc * NXM + 4 * xu) =
+                        make_float4(rv[4 * ii], rv[4 * ii + 1], rv[4 * ii + 2], rv[4 * ii + 3]);
+        } else {
+#pragma unroll
+            for (int ii = 0; ii < 4 * CR; ++ii)
+                if (row_unit(tid + (4 * i0 + ii) * NT, rc, xu)) mrow[rc * NXM + xu] = rv[ii];
+        }
+    };
+    if (ROW1) rows_load(0);
     // the parts of the stage combination that do not depend on this stage's
     // k: m0 + dtau sum_{j<s} a_j k_j and sum_{j<s} e_j k_j at this thread's
     // cells.  Up to eight cells per thread: KB of the k's for ITC cells per
@@ -600,7 +657,6 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
     constexpr int MAXIT = (2 * RP * NXM + NT - 1) / NT;
     const int nrow = min(2 * RP, g.nrows - rb);
     const int ncb = nrow * nx;
-    const float rnx = 1.0f / (float)nx;
     float px_[MAXIT], py_[MAXIT], pz_[MAXIT], ex_[MAXIT], ey_[MAXIT], ez_[MAXIT];
     float mnx[MAXIT], mny[MAXIT], mnz[MAXIT];   // the new stage state, held until the staged rows are free
     constexpr int KP = kMaxK - 1;
@@ -709,36 +765,14 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
     // ---- LDS stores and fix-ups
     twc.store(tw, tid);
     twf.store(tws, tid);
-    if (ROW1 && vec4) {
+    if (ROW1) {
+        rows_store(0);
+    } else {
+        // longest staged rows: rounds of eight units
 #pragma unroll
-        for (int it = 0; it < (ROW1 ? ITR : 1); ++it)
-            if (rd[it] >= 0) *reinterpret_cast<float4*>(mrow + rd[it]) = rv[it];
-    } else if (vec4) {
-        // longest staged rows: rounds of eight loads
-#pragma unroll
-        for (int i0 = 0; i0 < ITR; i0 += 8) {
-            float4 v[8];
-            int d[8];
-#pragma unroll
-            for (int ii = 0; ii < 8; ++ii) {
-                d[ii] = -1;
-                if (i0 + ii < ITR) row_load(tid + (i0 + ii) * NT, v[ii], d[ii]);
-            }
-#pragma unroll
-            for (int ii = 0; ii < 8; ++ii)
-                if (d[ii] >= 0) *reinterpret_cast<float4*>(mrow + d[ii]) = v[ii];
-        }
-    } else if (!BIG) {
-        for (int rq = 0; rq < R::NR; ++rq) {
-            bool ok;
-            const int row = staged_row(rq, ok);
-            const float* src = mi + row * nx;
-            float* dst = mrow + rq * 3 * NXM;
-            for (int t = tid; t < 3 * nx; t += NT) {
-                const int c = t >= nx ? (t >= 2 * nx ? 2 : 1) : 0;
-                const int x = t - c * nx;
-                dst[c * NXM + x] = ok ? src[c * cs + x] : 0.f;
-            }
+        for (int i0 = 0; i0 < ITR; i0 += CR) {
+            rows_load(i0);
+            rows_store(i0);
         }
     }
     float2 z[E2];
@@ -770,6 +804,8 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
             }
         }
     }
+    if (!EARLY && sr.done()) return;
+    const uint64_t step = sr.step();
     __syncthreads();   // twiddles and staged rows
     if (p.demag_on) F::template run<true>(z, scr + gi * R::SC, tws, lg);
     if constexpr (R::XALIAS) __syncthreads();   // every transform has left the scratch
@@ -839,7 +875,7 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
         }
         const int qq = r * nx + x;
         if (sa.mode == ROW_EVAL) {
-            float* h = sa.h_out;
+            float* h = global_ptr(sa.h_out);
             h[qq] = hx * p.Ms; h[cs + qq] = hy * p.Ms; h[2 * cs + qq] = hz * p.Ms;
             bad |= !(isfinite(hx) && isfinite(hy) && isfinite(hz));
             continue;
@@ -927,7 +963,8 @@ __global__ __launch_bounds__((RowSplit<PX, E2, NQ>::NT)) void row_inv_fast(Grid 
                                                             float2* __restrict__ S, StageArgs sa,
                                                             DevState* __restrict__ st) {
     extern __shared__ char dyn_lds[];
-    row_inv_body<PX, E2, NQ, XPER, NAT>(g, p, twx, S, sa, st, xcd_remap_blocks(blockIdx.x, gridDim.x), dyn_lds);
+    const int b = touch_args<sizeof(Grid) + sizeof(Phys) + 16 + sizeof(StageArgs)>(blockIdx.x);
+    row_inv_body<PX, E2, NQ, XPER, NAT>(g, p, twx, S, sa, st, xcd_remap_blocks(b, gridDim.x), dyn_lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -998,7 +1035,9 @@ __device__ __forceinline__ void col2d_body(const Col2dArgs& a, DevState* __restr
     float2* xst = (float2*)(lds + CF::O_XST);
     float2* scr = (float2*)(lds + CF::O_SCR);
     float2* xch = (float2*)(lds + CF::O_XCH);
-    if (st->done) return;
+    const StateRead<!BIG> sr(st);
+    if (BIG || gridDim.x >= kManyBlocks)
+        if (st->done) return;
     const int tid = threadIdx.x;
     // a group that fills its wavefront: the group index is wave-uniform
     const int gi = P == 64 ? __builtin_amdgcn_readfirstlane(tid / P) : tid / P;
@@ -1120,6 +1159,7 @@ __device__ __forceinline__ void col2d_body(const Col2dArgs& a, DevState* __restr
             }
         }
     }
+    if (!BIG && sr.done()) return;
     __syncthreads();   // stage twiddles (and the staged columns)
     if constexpr (!BIG) {
         // every LDS read first (the staged columns hold zeros at y >= ny;
@@ -1248,7 +1288,8 @@ __device__ __forceinline__ void col2d_body(const Col2dArgs& a, DevState* __restr
 template <int L, int E, int NQ>
 __global__ __launch_bounds__((ColSplit<L, E, NQ>::NT)) void col2d_fast(Col2dArgs a, DevState* __restrict__ st) {
     extern __shared__ char dyn_lds[];
-    col2d_body<L, E, NQ>(a, st, xcd_remap_blocks(blockIdx.x, gridDim.x), dyn_lds);
+    const int b = touch_args<sizeof(Col2dArgs)>(blockIdx.x);
+    col2d_body<L, E, NQ>(a, st, xcd_remap_blocks(b, gridDim.x), dyn_lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1296,7 +1337,8 @@ __global__ __launch_bounds__((RowSplit<PX, E2, NQ>::NT)) void row_fwd_group(cons
     extern __shared__ char dyn_lds[];
     const int2 m = map[blockIdx.x];
     const FilmRow& f = films[m.x];
-    row_fwd_body<PX, E2, NQ, false, false>(f.g, f.twx, f.S, f.fa, f.st, m.y, dyn_lds);
+    const int b = touch_lines<sizeof(FilmRow)>((const uint32_t*)&f, m.y);
+    row_fwd_body<PX, E2, NQ, false, false>(f.g, global_ptr(f.twx), global_ptr(f.S), f.fa, global_ptr(f.st), b, dyn_lds);
 }
 
 template <int PX, int E2, int NQ>
@@ -1305,7 +1347,8 @@ __global__ __launch_bounds__((RowSplit<PX, E2, NQ>::NT)) void row_inv_group(cons
     extern __shared__ char dyn_lds[];
     const int2 m = map[blockIdx.x];
     const FilmRow& f = films[m.x];
-    row_inv_body<PX, E2, NQ, false, false>(f.g, f.p, f.twx, f.S, f.sa, f.st, m.y, dyn_lds);
+    const int b = touch_lines<sizeof(FilmRow)>((const uint32_t*)&f, m.y);
+    row_inv_body<PX, E2, NQ, false, false>(f.g, f.p, global_ptr(f.twx), global_ptr(f.S), f.sa, global_ptr(f.st), b, dyn_lds);
 }
 
 template <int L, int E, int NQ>
@@ -1314,7 +1357,12 @@ __global__ __launch_bounds__((ColSplit<L, E, NQ>::NT)) void col_group(const Film
     extern __shared__ char dyn_lds[];
     const int2 m = map[blockIdx.x];
     const FilmCol& f = films[m.x];
-    col2d_body<L, E, NQ>(f.a, f.st, m.y, dyn_lds);
+    const int b = touch_lines<sizeof(FilmCol)>((const uint32_t*)&f, m.y);
+    Col2dArgs a = f.a;
+    a.S = global_ptr(a.S);
+    a.K = global_ptr(a.K);
+    a.tw = global_ptr(a.tw);
+    col2d_body<L, E, NQ>(a, global_ptr(f.st), b, dyn_lds);
 }
 
 // LDS of one workgroup on gfx950

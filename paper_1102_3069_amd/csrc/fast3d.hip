@@ -86,7 +86,7 @@ __global__ __launch_bounds__((Tile3<L, E, TW, H, NC>::NT)) void col3_tiled(ColAr
     float2* X = lds + T::O_X;
     if (st->done) return;
     const int tid = threadIdx.x;
-    int lb = xcd_remap_blocks(blockIdx.x, gridDim.x);
+    int lb = xcd_remap_blocks(touch_args<sizeof(ColArgs)>(blockIdx.x), gridDim.x);
     const int per_c = a.nouter * a.ntiles;      // blocks of one component (NC = 1)
     const int c0 = NC == 3 ? 0 : lb / per_c;    // first component of the block
     lb -= c0 * per_c;
