@@ -201,19 +201,59 @@ __device__ double entry_from_reps(int comp, const Reps& rx, const Reps& ry, cons
     return v;
 }
 
-__global__ void tensor_grid_kernel(double2* out, int comp, TensorGeom tg) {
+// The tensor is even or odd in each offset, so only the non-negative offsets
+// are computed (each takes 27 or 216 nodes, and an image sum on periodic
+// grids): m[a] = n (open) or n / 2 + 1 (periodic) of them per axis.
+struct Octant {
+    int m[3];
+};
+
+__global__ void tensor_octant_kernel(double* oct, int comp, TensorGeom tg, Octant q) {
+    const long long tot = (long long)q.m[0] * q.m[1] * q.m[2];
+    const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (id >= tot) return;
+    const int ix = (int)(id % q.m[0]);
+    const int iy = (int)((id / q.m[0]) % q.m[1]);
+    const int iz = (int)(id / ((long long)q.m[0] * q.m[1]));
+    oct[id] = entry_from_reps(comp, axis_reps(ix, tg.n[0], tg.P[0], tg.pbc[0]),
+                              axis_reps(iy, tg.n[1], tg.P[1], tg.pbc[1]),
+                              axis_reps(iz, tg.n[2], tg.P[2], tg.pbc[2]), tg);
+}
+
+// place of FFT-grid index idx among the non-negative offsets (-1: the zero
+// gap of a padded axis); neg: the offset is negative
+__device__ int octant_index(int idx, int n, int P, int periodic, bool& neg) {
+    neg = false;
+    if (periodic) {
+        if (idx <= n / 2) return idx;
+        neg = true;
+        return n - idx;
+    }
+    if (idx < n) return idx;
+    neg = true;
+    return idx > P - n ? P - idx : -1;
+}
+
+__global__ void tensor_grid_kernel(double2* out, const double* oct, int comp, TensorGeom tg, Octant q) {
     const long long tot = (long long)tg.P[0] * tg.P[1] * tg.P[2];
     const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (id >= tot) return;
-    const int ix = (int)(id % tg.P[0]);
-    const int iy = (int)((id / tg.P[0]) % tg.P[1]);
-    const int iz = (int)(id / ((long long)tg.P[0] * tg.P[1]));
-    const Reps rx = axis_reps(ix, tg.n[0], tg.P[0], tg.pbc[0]);
-    const Reps ry = axis_reps(iy, tg.n[1], tg.P[1], tg.pbc[1]);
-    const Reps rz = axis_reps(iz, tg.n[2], tg.P[2], tg.pbc[2]);
-    double2 v;
-    v.x = (rx.n && ry.n && rz.n) ? entry_from_reps(comp, rx, ry, rz, tg) : 0.0;
-    v.y = 0.0;
+    const int i[3] = {(int)(id % tg.P[0]), (int)((id / tg.P[0]) % tg.P[1]),
+                      (int)(id / ((long long)tg.P[0] * tg.P[1]))};
+    // xy is odd in x and y, xz in x and z, yz in y and z
+    const bool odd[3] = {comp == 3 || comp == 4, comp == 3 || comp == 5, comp >= 4};
+    int c[3];
+    bool minus = false;
+    for (int a = 0; a < 3; ++a) {
+        bool neg;
+        c[a] = octant_index(i[a], tg.n[a], tg.P[a], tg.pbc[a], neg);
+        minus ^= neg && odd[a];
+    }
+    double2 v = {0.0, 0.0};
+    if (c[0] >= 0 && c[1] >= 0 && c[2] >= 0) {
+        v.x = oct[((long long)c[2] * q.m[1] + c[1]) * q.m[0] + c[0]];
+        if (minus) v.x = -v.x;
+    }
     out[id] = v;
 }
 
@@ -258,13 +298,29 @@ __global__ __launch_bounds__(TT) void fft_lines_f64(double2* data, int nlines, i
 }
 
 // max |Re| and |Im| over the spectrum (bit patterns of non-negative doubles
-// order like the values)
+// order like the values), one atomic per wavefront
 __global__ void spectrum_residue_kernel(const double2* spec, long long tot, unsigned long long* mx) {
-    const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= tot) return;
-    const double2 v = spec[id];
-    atomicMax(&mx[0], (unsigned long long)__double_as_longlong(fabs(v.x)));
-    atomicMax(&mx[1], (unsigned long long)__double_as_longlong(fabs(v.y)));
+    double re = 0.0, im = 0.0;
+    bool bad = false;
+    for (long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x; id < tot;
+         id += (long long)gridDim.x * blockDim.x) {
+        const double2 v = spec[id];
+        bad |= !isfinite(v.x) || !isfinite(v.y);
+        re = fmax(re, fabs(v.x));
+        im = fmax(im, fabs(v.y));
+    }
+    if (bad) re = im = NAN;    // (its bits order above every finite value)
+    unsigned long long r = (unsigned long long)__double_as_longlong(fabs(re));
+    unsigned long long m = (unsigned long long)__double_as_longlong(fabs(im));
+    for (int off = 32; off > 0; off >>= 1) {
+        const unsigned long long r2 = __shfl_xor(r, off), m2 = __shfl_xor(m, off);
+        r = r2 > r ? r2 : r;
+        m = m2 > m ? m2 : m;
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicMax(&mx[0], r);
+        atomicMax(&mx[1], m);
+    }
 }
 
 // K[comp][o'][kx][a'] = scale * Re spec(kx, ky, kz); 2D: a = y, o = z (one
@@ -353,20 +409,27 @@ hipError_t build_kernel_spectrum(const Grid& g, const TensorGeom& tg, float* K, 
     unsigned long long* mx = nullptr;
     unsigned long long hm[2];
     double worst = 0.0;
+    Octant q;
+    for (int a = 0; a < 3; ++a) q.m[a] = tg.pbc[a] ? tg.n[a] / 2 + 1 : tg.n[a];
+    const long long otot = (long long)q.m[0] * q.m[1] * q.m[2];
+    double* oct = nullptr;
     TRY(hipMalloc(&buf, sizeof(double2) * tot));
+    TRY(hipMalloc(&oct, sizeof(double) * otot));
     TRY(hipMalloc(&mx, 2 * sizeof(unsigned long long)));
     TRY(make_tw64(Px, &twx));
     TRY(make_tw64(Py, &twy));
     TRY(make_tw64(Pz, &twz));
     for (int c = 0; c < ncomp; ++c) {
         const int blocks = (int)((tot + TT - 1) / TT);
-        hipLaunchKernelGGL(tensor_grid_kernel, dim3(blocks), dim3(TT), 0, s, buf, c, tg);
+        hipLaunchKernelGGL(tensor_octant_kernel, dim3((int)((otot + TT - 1) / TT)), dim3(TT), 0, s, oct, c, tg, q);
+        TRY(hipGetLastError());
+        hipLaunchKernelGGL(tensor_grid_kernel, dim3(blocks), dim3(TT), 0, s, buf, oct, c, tg, q);
         TRY(hipGetLastError());
         TRY(fft_axis_f64(buf, Px, Py, Pz, 0, twx, s));
         TRY(fft_axis_f64(buf, Px, Py, Pz, 1, twy, s));
         TRY(fft_axis_f64(buf, Px, Py, Pz, 2, twz, s));
         TRY(hipMemsetAsync(mx, 0, 2 * sizeof(unsigned long long), s));
-        hipLaunchKernelGGL(spectrum_residue_kernel, dim3(blocks), dim3(TT), 0, s, buf, tot, mx);
+        hipLaunchKernelGGL(spectrum_residue_kernel, dim3(blocks < 2048 ? blocks : 2048), dim3(TT), 0, s, buf, tot, mx);
         TRY(hipGetLastError());
         const long long ctot = (long long)no_c * nkx * na_c;
         hipLaunchKernelGGL(compress_kernel, dim3((int)((ctot + TT - 1) / TT)), dim3(TT), 0, s, buf, K, c,
@@ -384,6 +447,7 @@ hipError_t build_kernel_spectrum(const Grid& g, const TensorGeom& tg, float* K, 
     if (resid_out) *resid_out = worst;
 done:
     if (buf) (void)hipFree(buf);
+    if (oct) (void)hipFree(oct);
     if (mx) (void)hipFree(mx);
     if (twx) (void)hipFree(twx);
     if (twy) (void)hipFree(twy);
