@@ -805,7 +805,7 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
         }
     }
     if (!EARLY && sr.done()) return;
-    const uint64_t step = sr.step();
+    const uint64_t step = sr.step() + (uint64_t)sa.step_add;
     __syncthreads();   // twiddles and staged rows
     if (p.demag_on) F::template run<true>(z, scr + gi * R::SC, tws, lg);
     if constexpr (R::XALIAS) __syncthreads();   // every transform has left the scratch

@@ -241,17 +241,102 @@ __global__ __launch_bounds__((Tile3<L, E, TW, H, NC>::NT)) void col3_tiled(ColAr
     }
 }
 
+// ---------------------------------------------------------------------------
+// z pass of a thin open grid (N = 2 ... 8 planes, Pz = 2 N): one thread per
+// (kx, ky) holds the N planes of the three components in registers, takes
+// the even and the odd half of the 2N-point transform as two N-point DFTs
+// (X[2k] = DFT_N(x), X[2k+1] = DFT_N(x W^n)), multiplies and transforms back.
+// Nothing passes through LDS; consecutive threads read consecutive kx.  The
+// runtime-length kernel spends its time on index arithmetic and barriers at
+// these lengths (41 us a call at 256 x 64 x 2 cells; the whole adaptive run of
+// 154 Bogacki-Shampine attempts there 38.6 -> 16.1 ms).
+// ---------------------------------------------------------------------------
+constexpr int kThinThreads = 256;
+
+template <int N>
+__global__ __launch_bounds__(kThinThreads) void thin_z(ColArgs a, DevState* __restrict__ st) {
+    if (st->done) return;
+    const int b = xcd_remap_blocks(touch_args<sizeof(ColArgs)>(blockIdx.x), gridDim.x);
+    const int id = b * kThinThreads + (int)threadIdx.x;
+    if (id >= a.nouter * a.nkx) return;
+    // mirror pairs (ko, Po - ko) of rows one after the other: they share
+    // kernel rows
+    const int op = id / a.nkx, kx = id - op * a.nkx;
+    const int ko = mirror_pair_order(op, a.Po);
+    const int o = a.o_split ? (ko & 1) * (a.Po / 2) + (ko >> 1) : ko;
+    const float2* in = a.in + (long long)o * a.os_in + kx;
+    float2* out = a.out + (long long)o * a.os_out + kx;
+    float2 x[3][N], acc[3][N];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int n = 0; n < N; ++n) x[c][n] = in[c * a.cs_in + n * a.as_in];
+    // kernel entries at ka = 0 ... N of this (kx, ko), mirror compressed along y
+    const bool fo = ko > a.Po - ko;
+    const int io = fo ? a.Po - ko : ko;
+    const long long cstride = (long long)a.no_c * a.nkx * a.na_c;
+    const float* K = a.K + ((long long)io * a.nkx + kx) * a.na_c;
+    float Kv[6][N + 1];
+#pragma unroll
+    for (int c = 0; c < 6; ++c)
+#pragma unroll
+        for (int i = 0; i <= N; ++i) Kv[c][i] = K[c * cstride + i];
+#pragma unroll
+    for (int c = 0; c < 6; ++c)
+        if (fo && a.sign_o[c] < 0)
+#pragma unroll
+            for (int i = 0; i <= N; ++i) Kv[c][i] = -Kv[c][i];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        float2 y[3][N];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+#pragma unroll
+            for (int n = 0; n < N; ++n) y[c][n] = h && n ? cmul(x[c][n], a.tw[n]) : x[c][n];
+            Dft<N, float2>::run(y[c], false);
+        }
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+            const int ka = 2 * k + h;                 // past N: the mirror entry, odd components (xz, yz) negated
+            const int ia = ka > N ? 2 * N - ka : ka;
+            const float sg = ka > N ? -1.f : 1.f;
+            const float xx = Kv[0][ia], yy = Kv[1][ia], zz = Kv[2][ia], xy = Kv[3][ia], xz = sg * Kv[4][ia],
+                        yz = sg * Kv[5][ia];
+            const float2 Mx = y[0][k], My = y[1][k], Mz = y[2][k];
+            y[0][k] = make_float2(xx * Mx.x + xy * My.x + xz * Mz.x, xx * Mx.y + xy * My.y + xz * Mz.y);
+            y[1][k] = make_float2(xy * Mx.x + yy * My.x + yz * Mz.x, xy * Mx.y + yy * My.y + yz * Mz.y);
+            y[2][k] = make_float2(xz * Mx.x + yz * My.x + zz * Mz.x, xz * Mx.y + yz * My.y + zz * Mz.y);
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            Dft<N, float2>::run(y[c], true);
+#pragma unroll
+            for (int n = 0; n < N; ++n) {
+                const float2 v = h && n ? cmul(y[c][n], cconj(a.tw[n])) : y[c][n];
+                acc[c][n] = h ? cadd(acc[c][n], v) : v;
+            }
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int n = 0; n < N; ++n) out[c * a.cs_out + n * a.as_out] = acc[c][n];
+}
+
 // compiled (length L of one transform, elements per lane, tile width,
-// halves): open axes of 2 L = 32 ... 512, periodic axes of L = 32 ... 256.
+// halves): open axes of 2 L = 32 ... 1024 (the pass with the product: 512),
+// periodic axes of L = 32 ... 256.
 // T3_FULL: the pass with the kernel product (three components per block);
 // T3_ONE: the plain forward and inverse passes (one component per block,
 // tiles twice as wide where that fits)
-#define T3_FULL(X)                                                                                  \
-    X(16, 4, 16, 2) X(32, 4, 8, 2) X(64, 8, 4, 2) X(128, 8, 4, 2) X(256, 16, 4, 2) X(32, 4, 16, 1) \
-    X(64, 8, 16, 1) X(128, 8, 8, 1) X(256, 16, 8, 1)
-#define T3_ONE(X)                                                                                     \
-    X(16, 4, 32, 2) X(32, 4, 16, 2) X(64, 8, 16, 2) X(128, 8, 8, 2) X(256, 16, 8, 2) X(32, 4, 32, 1) \
-    X(64, 8, 32, 1) X(128, 8, 16, 1) X(256, 16, 16, 1)
+#define T3_FULL(X)                                                                                     \
+    X(16, 4, 16, 2) X(24, 12, 16, 2) X(32, 4, 8, 2) X(48, 12, 8, 2) X(64, 8, 4, 2) X(96, 12, 4, 2)     \
+    X(128, 8, 4, 2) X(192, 12, 4, 2) X(256, 16, 4, 2) X(32, 4, 16, 1) X(64, 8, 16, 1) X(128, 8, 8, 1) \
+    X(256, 16, 8, 1)
+#define T3_ONE(X)                                                                                       \
+    X(16, 4, 32, 2) X(24, 12, 32, 2) X(32, 4, 16, 2) X(48, 12, 16, 2) X(64, 8, 16, 2) X(96, 12, 16, 2)  \
+    X(128, 8, 8, 2) X(192, 12, 8, 2) X(256, 16, 8, 2) X(384, 12, 4, 2) X(512, 16, 4, 2) X(32, 4, 32, 1) \
+    X(48, 12, 32, 1) X(64, 8, 32, 1) X(96, 12, 16, 1) X(128, 8, 16, 1) X(192, 12, 16, 1) X(256, 16, 16, 1)
 
 hipError_t allow_lds3(const void* fn, int bytes) { return raise_lds_limit(fn, bytes); }
 
@@ -309,6 +394,38 @@ int fast3d_col_width(int P, int split, bool full) {
 #undef CASE
     }
     return 0;
+}
+
+// shortest compiled transform of an open axis with L >= n (0: none)
+int fast3d_len_at_least(int n, bool full) {
+    int best = 0;
+#define CASE(LL, E, TW, HH) if (HH == 2 && LL >= n && (best == 0 || LL < best)) best = LL;
+    if (full) {
+        T3_FULL(CASE)
+    } else {
+        T3_ONE(CASE)
+    }
+#undef CASE
+    return best;
+}
+
+bool fast3d_thin_ok(int nz, int Pz, int split) { return split && nz >= 2 && nz <= 8 && Pz == 2 * nz; }
+
+hipError_t launch_thin_z(const ColArgs& a, DevState* st, hipStream_t s) {
+    if (!fast3d_thin_ok(a.n_in, a.P, a.split) || a.n_out != a.n_in || a.ncomp != 6 || a.nouter != a.Po ||
+        a.na_c != a.n_in + 1 || a.Pa != a.P)
+        return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((a.nouter * a.nkx + kThinThreads - 1) / kThinThreads)), block(kThinThreads);
+    switch (a.n_in) {
+        case 2: hot_launch(thin_z<2>, grid, block, 0, s, a, st); break;
+        case 3: hot_launch(thin_z<3>, grid, block, 0, s, a, st); break;
+        case 4: hot_launch(thin_z<4>, grid, block, 0, s, a, st); break;
+        case 5: hot_launch(thin_z<5>, grid, block, 0, s, a, st); break;
+        case 6: hot_launch(thin_z<6>, grid, block, 0, s, a, st); break;
+        case 7: hot_launch(thin_z<7>, grid, block, 0, s, a, st); break;
+        default: hot_launch(thin_z<8>, grid, block, 0, s, a, st); break;
+    }
+    return hipGetLastError();
 }
 
 // a.P the axis FFT length, a.split for an open axis; COL_FWD: n_in <= L

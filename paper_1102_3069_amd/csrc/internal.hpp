@@ -207,6 +207,7 @@ struct StageArgs {
     int with_err;            // ROW_STAGE: also the embedded error estimate;
                              // ROW_KONLY: also max over cells |k| (into err_bits)
     int skip_fwd;            // ROW_STAGE: no forward transform of the new state
+    int step_add;            // steps taken since the device state's step counter was written
     BufRef m_in;             // stage input m_s
     BufRef m0;               // state at the start of the step
     BufRef m_out;            // next stage input / new state
@@ -267,10 +268,11 @@ hipError_t launch_row_fwd(const Grid& g, const Phys& p, const FftPlan& px, const
 hipError_t launch_row_inv(const Grid& g, const Phys& p, const FftPlan& px, const float2* twx,
                           float2* S, const StageArgs& sa, DevState* st, hipStream_t s);
 hipError_t launch_col(const ColArgs& a, DevState* st, int mode, hipStream_t s);
-hipError_t launch_ctrl_fixed(DevState* st, int evals, double dt, hipStream_t s);
-hipError_t launch_ctrl_dm(DevState* st, hipStream_t s);
-hipError_t launch_ctrl_dm_accept(DevState* st, int evals, hipStream_t s);
-hipError_t launch_ctrl_dp45(DevState* st, hipStream_t s);
+hipError_t launch_ctrl_fixed(DevState* st, int evals, int steps, hipStream_t s);
+// progress (pinned host memory): 2 nattempt + done after each step or attempt
+hipError_t launch_ctrl_dm(DevState* st, unsigned long long* progress, hipStream_t s);
+hipError_t launch_ctrl_dm_accept(DevState* st, int evals, unsigned long long* progress, hipStream_t s);
+hipError_t launch_ctrl_dp45(DevState* st, unsigned long long* progress, hipStream_t s);
 hipError_t launch_state_add_evals(DevState* st, int evals, hipStream_t s);
 hipError_t launch_check_unit(const float* m, int ncells, int* bad, hipStream_t s);
 hipError_t launch_normalize_check(float* m, int ncells, int* bad, hipStream_t s);
@@ -320,6 +322,10 @@ bool fast2d_variant_shape(int kind, int len, int var, int* elems, int* classes);
 bool fast3d_col_ok(int P, int split, bool full);     // full: the pass with the kernel product
 int fast3d_col_width(int P, int split, bool full);
 hipError_t launch_col3_tiled(const ColArgs& a, int mode, DevState* st, hipStream_t s);
+int fast3d_len_at_least(int n, bool full);           // shortest compiled open-axis transform L >= n (0: none)
+// z pass with the product for open grids of 2 ... 8 planes
+bool fast3d_thin_ok(int nz, int Pz, int split);
+hipError_t launch_thin_z(const ColArgs& a, DevState* st, hipStream_t s);
 int fast2d_row_len_at_least(int n);
 int fast2d_col_len_at_least(int n);
 int fast2d_col_width(int L, int var = -1);

@@ -150,7 +150,7 @@ __global__ __launch_bounds__(RT) void row_inv_kernel(Grid g, Phys p, FftPlan px,
     constexpr int MAXC = (MAXE + 2) / 3;
     const int cur = st->cur;
     const float dtau = st->dtau;
-    const uint64_t step = (uint64_t)st->step;
+    const uint64_t step = (uint64_t)st->step + (uint64_t)sa.step_add;
     const int tid = threadIdx.x;
     const int r0 = 2 * blockIdx.x;
     const bool has1 = r0 + 1 < g.nrows;
@@ -426,26 +426,39 @@ __global__ __launch_bounds__(CT) void col_kernel(ColArgs a, DevState* __restrict
 // ---------------------------------------------------------------------------
 // controllers (one thread)
 // ---------------------------------------------------------------------------
-__global__ void ctrl_fixed_kernel(DevState* st, int evals) {
+// end of `steps` fixed steps of `evals` evaluations each
+__global__ void ctrl_fixed_kernel(DevState* st, int evals, int steps) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    st->t += st->dt;
-    st->cur ^= 1;
-    st->step += 1;
-    st->nsteps += 1;
-    st->nevals += evals;
+    double t = st->t;
+    for (int i = 0; i < steps; ++i) t += st->dt;
+    st->t = t;
+    st->cur ^= steps & 1;
+    st->step += steps;
+    st->nsteps += steps;
+    st->nevals += (long long)evals * steps;
+}
+
+// tells the host, which polls this word, how far an adaptive run is
+__device__ __forceinline__ void publish(unsigned long long* progress, long long nattempt, int done) {
+    __hip_atomic_store(progress, (unsigned long long)nattempt << 1 | (done ? 1u : 0u), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Fixed tableau with a bounded change of m per step: the first stage of a
 // step left max over cells |k_1| in err_bits (k in units of dtau); the
 // step is max_dm / that (tol holds max_dm), at most dt_max, and the last
 // one lands on t_end.
-__global__ void ctrl_dm_kernel(DevState* st) {
+__global__ void ctrl_dm_kernel(DevState* st, unsigned long long* progress) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     if (st->done) return;
     const float kf = __uint_as_float(st->err_bits);
     st->err_bits = 0u;
     st->last_err = (double)kf;
-    if (st->health) { st->done = 1; return; }
+    if (st->health) {
+        st->done = 1;
+        publish(progress, st->nattempt, 1);
+        return;
+    }
     double dt = st->dt_max;
     if (kf > 0.f) dt = fmin(dt, st->tol / ((double)kf * st->gms));
     const double rem = st->t_end - st->t;
@@ -457,7 +470,7 @@ __global__ void ctrl_dm_kernel(DevState* st) {
 }
 
 // end of such a step: the new state is in place
-__global__ void ctrl_dm_accept_kernel(DevState* st, int evals) {
+__global__ void ctrl_dm_accept_kernel(DevState* st, int evals, unsigned long long* progress) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     if (st->done) return;
     const long long a = st->nattempt++;
@@ -469,12 +482,15 @@ __global__ void ctrl_dm_accept_kernel(DevState* st, int evals) {
         st->log[a] = r;
     }
     st->nevals += evals;
-    if (st->health) { st->done = 1; return; }
-    st->t = st->clipped ? st->t_end : st->t + st->dt;
-    st->cur ^= 1;
-    st->step += 1;
-    st->nsteps += 1;
-    if (st->clipped) st->done = 1;
+    const bool end = st->health || st->clipped;
+    if (!st->health) {
+        st->t = st->clipped ? st->t_end : st->t + st->dt;
+        st->cur ^= 1;
+        st->step += 1;
+        st->nsteps += 1;
+    }
+    if (end) st->done = 1;
+    publish(progress, a + 1, end);
 }
 
 __global__ void ctrl_fixed_group_kernel(DevState* states, int nfilms, int evals) {
@@ -493,7 +509,7 @@ __global__ void ctrl_fixed_group_kernel(DevState* states, int nfilms, int evals)
 // record is read into registers in one round of loads, updated there and
 // written back once (the single thread would otherwise wait on one global
 // read after another).
-__device__ void dp45_control(DevState* st) {
+__device__ void dp45_control(DevState* st, unsigned long long* progress) {
     DevState h = *st;
     // a finished run is left as it is: the decisions below are computed
     // either way (register arithmetic only) and the stores skipped, so that
@@ -535,6 +551,7 @@ __device__ void dp45_control(DevState* st) {
         }
     }
     if (!live) return;
+    if (progress) publish(progress, h.nattempt, h.done);
     if (a < h.log_cap && h.log) {
         llg_attempt r;
         r.dt = dt_att;
@@ -545,15 +562,15 @@ __device__ void dp45_control(DevState* st) {
     *st = h;
 }
 
-__global__ void ctrl_dp45_kernel(DevState* st) {
+__global__ void ctrl_dp45_kernel(DevState* st, unsigned long long* progress) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    dp45_control(st);
+    dp45_control(st, progress);
 }
 
 // one thread per film of a batch
 __global__ void ctrl_dp45_group_kernel(DevState* states, int nfilms) {
     const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    if (f < nfilms) dp45_control(states + f);
+    if (f < nfilms) dp45_control(states + f, nullptr);
 }
 
 __global__ void state_add_evals_kernel(DevState* st, int evals) {
@@ -677,9 +694,8 @@ hipError_t launch_col(const ColArgs& a, DevState* st, int mode, hipStream_t s) {
     }
 }
 
-hipError_t launch_ctrl_fixed(DevState* st, int evals, double dt, hipStream_t s) {
-    (void)dt;
-    hipLaunchKernelGGL(ctrl_fixed_kernel, dim3(1), dim3(64), 0, s, st, evals);
+hipError_t launch_ctrl_fixed(DevState* st, int evals, int steps, hipStream_t s) {
+    hipLaunchKernelGGL(ctrl_fixed_kernel, dim3(1), dim3(64), 0, s, st, evals, steps);
     return hipGetLastError();
 }
 
@@ -688,18 +704,18 @@ hipError_t launch_ctrl_fixed_group(DevState* states, int nfilms, int evals, hipS
     return hipGetLastError();
 }
 
-hipError_t launch_ctrl_dp45(DevState* st, hipStream_t s) {
-    hipLaunchKernelGGL(ctrl_dp45_kernel, dim3(1), dim3(64), 0, s, st);
+hipError_t launch_ctrl_dp45(DevState* st, unsigned long long* progress, hipStream_t s) {
+    hipLaunchKernelGGL(ctrl_dp45_kernel, dim3(1), dim3(64), 0, s, st, progress);
     return hipGetLastError();
 }
 
-hipError_t launch_ctrl_dm(DevState* st, hipStream_t s) {
-    hipLaunchKernelGGL(ctrl_dm_kernel, dim3(1), dim3(64), 0, s, st);
+hipError_t launch_ctrl_dm(DevState* st, unsigned long long* progress, hipStream_t s) {
+    hipLaunchKernelGGL(ctrl_dm_kernel, dim3(1), dim3(64), 0, s, st, progress);
     return hipGetLastError();
 }
 
-hipError_t launch_ctrl_dm_accept(DevState* st, int evals, hipStream_t s) {
-    hipLaunchKernelGGL(ctrl_dm_accept_kernel, dim3(1), dim3(64), 0, s, st, evals);
+hipError_t launch_ctrl_dm_accept(DevState* st, int evals, unsigned long long* progress, hipStream_t s) {
+    hipLaunchKernelGGL(ctrl_dm_accept_kernel, dim3(1), dim3(64), 0, s, st, evals, progress);
     return hipGetLastError();
 }
 

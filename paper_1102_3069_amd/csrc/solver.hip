@@ -130,6 +130,7 @@ struct llg_solver {
     bool fastrows = false;    // row passes of compiled length (2D packed or 3D natural layout)
     bool fast3dy = false;     // 3D, y axis of compiled length: tiled y passes
     bool fast3dz = false;     // 3D, z axis of compiled length: tiled z pass
+    bool thinz = false;       // 3D, few planes along an open z: the z pass in registers
     // device buffers
     float* K = nullptr;
     bool K_valid = false;
@@ -148,11 +149,11 @@ struct llg_solver {
     bool spec_valid = false;   // S holds the forward x transform of m
     bool k1_valid = false;     // kfs[cur] holds f(m) for the adaptive method
     double last_dt = 0.0;
-    Graph gfix, gdp, gdm;
-    // the done flag of the last two launched chunks of step graphs, copied to
-    // pinned host memory behind each chunk (launch_until_done)
-    int* hflag = nullptr;
-    hipEvent_t flag_ev[2] = {nullptr, nullptr};
+    Graph gfix, gfixn, gdp, gdm;
+    // how far an adaptive run is (launch_until_done): pinned host memory the
+    // step controllers write, and its device address
+    unsigned long long* progress = nullptr;
+    unsigned long long* progress_dev = nullptr;
 };
 
 namespace {
@@ -181,6 +182,7 @@ void free_dev(void* p) {
 
 void invalidate_graphs(llg_solver* s) {
     s->gfix.reset();
+    s->gfixn.reset();
     s->gdp.reset();
     s->gdm.reset();
 }
@@ -232,7 +234,8 @@ size_t noalloc_need(const int n[3], const int P[3]) {
 // 512 x 128; at 1000 x 600 cells 322 (2000 x 1200 points) against 87 (2048 x
 // 1536); one evaluation of 100 x 37 cells 56 against 30.  The compiled
 // lengths are at most 3/2 apart, so the longer padding never costs what the
-// compiled kernels gain (3.3 to 3.7).  Kept as they are: a geometry whose
+// compiled kernels gain (3.3 to 3.7); 100 x 60 x 20 cells (256 x 128 x 48
+// points) 113 -> 50 us.  Kept as they are: a geometry whose
 // spectrum would outgrow the scratch of the no-allocation evaluation only
 // by the longer padding.
 void compiled_lengths(const int n[3], const int pb[3], int P[3]) {
@@ -245,6 +248,14 @@ void compiled_lengths(const int n[3], const int pb[3], int P[3]) {
         if (!fast2d_row_ok(px, 0, pb[0] != 0) || !fast2d_col_ok(l, 1, 0) || (px / 2) % fast2d_col_width(l, 0)) return;
         Q[0] = px;
         Q[1] = 2 * l;
+    } else {
+        // 3D: every axis by itself
+        const int px = pb[0] ? 0 : fast2d_row_len_at_least(P[0]);
+        if (px > 0 && px <= 2048 && fast2d_row_ok(px, 0, false)) Q[0] = px;
+        const int ly = pb[1] ? 0 : fast3d_len_at_least(P[1] / 2, false);
+        if (ly > 0) Q[1] = 2 * ly;
+        const int lz = pb[2] || fast3d_thin_ok(n[2], P[2], 1) ? 0 : fast3d_len_at_least(P[2] / 2, true);
+        if (lz > 0) Q[2] = 2 * lz;
     }
     if (noalloc_need(n, P) <= kNoAllocBytes && noalloc_need(n, Q) > kNoAllocBytes) return;
     for (int a = 0; a < 3; ++a) P[a] = Q[a];
@@ -405,7 +416,9 @@ llg_status launch_spectral(llg_solver* s, const EvalBufs& b, hipEvent_t* ev_afte
     const int sz_[6] = {1, 1, 1, 1, -1, -1};   // along z: xz, yz odd
     const int sy_[6] = {1, 1, 1, -1, 1, -1};   // along y: xy, yz odd
     for (int c = 0; c < 6; ++c) { z.sign_a[c] = sz_[c]; z.sign_o[c] = sy_[c]; }
-    if (s->fast3dz) {
+    if (s->thinz) {
+        HIPCHK(s, launch_thin_z(z, b.st, s->stream));
+    } else if (s->fast3dz) {
         z.W = fast3d_col_width(g.Pz, g.split_z, true);
         z.ntiles = (g.nkx + z.W - 1) / z.W;
         HIPCHK(s, launch_col3_tiled(z, COL_FULL, b.st, s->stream));
@@ -479,34 +492,40 @@ llg_status restore_done(llg_solver* s, int was) {
     return write_state(s, &h);
 }
 
-// Launches a captured step graph in chunks of eight until the device state's
-// done flag is set or `max_launches` graphs have been launched (< 0: no
-// limit), then waits for the stream.  Behind each chunk the flag is copied
-// to pinned host memory and an event recorded; the host reads a chunk's
-// flag only after the next chunk is queued, so the device never waits for
-// the host between chunks.  Graphs launched after the flag was set do
-// nothing (every kernel of a step returns at once while it is set).
-llg_status launch_until_done(llg_solver* s, hipGraphExec_t exec, long long max_launches) {
-    constexpr int kChunk = 8;
+// Launches a captured step graph until the device state's done flag is set
+// or `max_launches` graphs have been launched (< 0: no limit), then waits for
+// the stream.  The step controller at the end of each graph writes the
+// attempt count (`base` at the start) and the flag to pinned host memory; the
+// host keeps kAhead graphs queued, so the device never waits for the host,
+// and at most kAhead - 1 graphs are launched past the end (they do nothing:
+// every kernel of a step returns while the flag is set, but each costs its
+// launches; chunks of eight wasted up to fifteen: 69 attempts at 512 x 512
+// 13.57 -> 13.20 ms, 10 at 2048 x 2048 27.24 -> 26.90 ms).  Should the stream run dry
+// without the expected count (a run that ended on a non-finite value between
+// two attempts), the wait below ends too.
+llg_status launch_until_done(llg_solver* s, hipGraphExec_t exec, long long base, long long max_launches) {
+    constexpr long long kAhead = 3;
+    volatile unsigned long long* progress = s->progress;
+    *progress = (unsigned long long)base << 1;
     long long launched = 0;
-    int pend = -1, slot = 0;
-    for (;;) {
-        int nl = kChunk;
-        if (max_launches >= 0 && max_launches - launched < nl) nl = (int)(max_launches - launched);
-        if (max_launches < 0 && launched > (1LL << 32)) nl = 0;
-        if (nl > 0) {
-            for (int i = 0; i < nl; ++i) HIPCHK(s, hipGraphLaunch(exec, s->stream));
-            launched += nl;
-            HIPCHK(s, hipMemcpyAsync(&s->hflag[slot], &s->st->done, sizeof(int), hipMemcpyDeviceToHost, s->stream));
-            HIPCHK(s, hipEventRecord(s->flag_ev[slot], s->stream));
+    for (unsigned spins = 0;;) {
+        const unsigned long long now = *progress;
+        if (now & 1) break;
+        const long long finished = (long long)(now >> 1) - base;
+        if (max_launches >= 0 && launched >= max_launches) break;
+        if (max_launches < 0 && launched > (1LL << 32)) break;
+        if (launched - finished < kAhead) {
+            HIPCHK(s, hipGraphLaunch(exec, s->stream));
+            ++launched;
+            spins = 0;
+            continue;
         }
-        if (pend >= 0) {
-            HIPCHK(s, hipEventSynchronize(s->flag_ev[pend]));
-            if (s->hflag[pend]) break;
+        if (++spins % 4096 == 0) {
+            const hipError_t e = hipStreamQuery(s->stream);
+            if (e == hipSuccess && *progress == now) break;
+            if (e != hipSuccess && e != hipErrorNotReady) HIPCHK(s, e);
         }
-        if (nl <= 0) break;
-        pend = slot;
-        slot ^= 1;
+        __builtin_ia32_pause();
     }
     return sync(s);
 }
@@ -532,31 +551,50 @@ llg_status eval_into(llg_solver* s, float* out, const Phys& p) {
 }
 
 
-// one fixed step of tableau t: S x (spectral + fused row pass) + controller
-llg_status enqueue_fixed_step(llg_solver* s, const Tableau& t, const Phys& p) {
+// `steps` fixed steps of tableau t: S x (spectral + fused row pass) each,
+// then the controller; odd steps find the state where an even one put it
+llg_status enqueue_fixed_steps(llg_solver* s, const Tableau& t, const Phys& p, int steps) {
     llg_status rc;
-    for (int st = 1; st <= t.S; ++st) {
-        if (p.demag_on && (rc = launch_spectral(s)) != LLG_OK) return rc;
-        StageArgs sa = {};
-        sa.mode = ROW_STAGE;
-        sa.m_in = st == 1 ? bref_cur(s->mbuf[0], s->mbuf[1], 1) : bref(s->ms[st % 2]);
-        sa.m0 = bref_cur(s->mbuf[0], s->mbuf[1], 1);
-        sa.m_out = st == t.S ? bref_cur(s->mbuf[0], s->mbuf[1], 2) : bref(s->ms[(st + 1) % 2]);
-        bool needed = false;
-        if (st < t.S) {
-            if (t.b[st - 1] != 0.0) needed = true;
-            for (int r = st; r < t.S; ++r)
-                if (t.A[r][st - 1] != 0.0) needed = true;
+    for (int i = 0; i < steps; ++i) {
+        for (int st = 1; st <= t.S; ++st) {
+            if (p.demag_on && (rc = launch_spectral(s)) != LLG_OK) return rc;
+            const int now = i % 2 ? 2 : 1, next = 3 - now;
+            StageArgs sa = {};
+            sa.mode = ROW_STAGE;
+            sa.step_add = i;
+            sa.m_in = st == 1 ? bref_cur(s->mbuf[0], s->mbuf[1], now) : bref(s->ms[st % 2]);
+            sa.m0 = bref_cur(s->mbuf[0], s->mbuf[1], now);
+            sa.m_out = st == t.S ? bref_cur(s->mbuf[0], s->mbuf[1], next) : bref(s->ms[(st + 1) % 2]);
+            bool needed = false;
+            if (st < t.S) {
+                if (t.b[st - 1] != 0.0) needed = true;
+                for (int r = st; r < t.S; ++r)
+                    if (t.A[r][st - 1] != 0.0) needed = true;
+            }
+            sa.k_out = bref(needed ? s->kb[st - 1] : nullptr);
+            sa.nk = st;
+            for (int j = 0; j < st; ++j) sa.a[j] = (float)(st < t.S ? t.A[st][j] : t.b[j]);
+            for (int j = 0; j + 1 < st; ++j) sa.kprev[j] = bref(s->kb[j]);
+            sa.h_out = nullptr;
+            HIPCHK(s, row_inv(s, p, sa));
         }
-        sa.k_out = bref(needed ? s->kb[st - 1] : nullptr);
-        sa.nk = st;
-        for (int j = 0; j < st; ++j) sa.a[j] = (float)(st < t.S ? t.A[st][j] : t.b[j]);
-        for (int j = 0; j + 1 < st; ++j) sa.kprev[j] = bref(s->kb[j]);
-        sa.h_out = nullptr;
-        HIPCHK(s, row_inv(s, p, sa));
     }
-    HIPCHK(s, launch_ctrl_fixed(s->st, t.S, 0.0, s->stream));
+    HIPCHK(s, launch_ctrl_fixed(s->st, t.S, steps, s->stream));
     return LLG_OK;
+}
+
+llg_status enqueue_fixed_step(llg_solver* s, const Tableau& t, const Phys& p) {
+    return enqueue_fixed_steps(s, t, p, 1);
+}
+
+// Long runs of fixed steps replay a graph of kStepsPerGraph steps with one
+// controller launch at its end: at 32 x 32 cells a step is a chain of five
+// launches of 4 to 8 us each, and the controller one of them (50 Heun steps
+// 1735 -> 1476 us).  A run must be at least twice that long to pay for the
+// longer capture.
+constexpr int kStepsPerGraph = 8;
+llg_status enqueue_fixed_chunk(llg_solver* s, const Tableau& t, const Phys& p) {
+    return enqueue_fixed_steps(s, t, p, kStepsPerGraph);
 }
 
 // one attempt of an embedded pair whose last stage is evaluated at the new
@@ -597,7 +635,7 @@ llg_status enqueue_fsal_attempt(llg_solver* s, const Tableau& t, const Phys& p) 
         }
         HIPCHK(s, row_inv(s, p, sa));
     }
-    HIPCHK(s, launch_ctrl_dp45(s->st, s->stream));
+    HIPCHK(s, launch_ctrl_dp45(s->st, s->progress_dev, s->stream));
     return LLG_OK;
 }
 
@@ -626,7 +664,7 @@ llg_status enqueue_plain_attempt(llg_solver* s, const Tableau& t, const Phys& p)
         }
         HIPCHK(s, row_inv(s, p, sa));
     }
-    HIPCHK(s, launch_ctrl_dp45(s->st, s->stream));
+    HIPCHK(s, launch_ctrl_dp45(s->st, s->progress_dev, s->stream));
     return LLG_OK;
 }
 
@@ -646,7 +684,7 @@ llg_status enqueue_dm_step(llg_solver* s, const Tableau& t, const Phys& p) {
     sk.m_out = bref(nullptr);
     sk.k_out = bref(s->kb[0]);
     HIPCHK(s, row_inv(s, p, sk));
-    HIPCHK(s, launch_ctrl_dm(s->st, s->stream));
+    HIPCHK(s, launch_ctrl_dm(s->st, s->progress_dev, s->stream));
     FwdArgs fa = {};
     fa.combine = 1;
     fa.a1 = (float)(S > 1 ? t.A[1][0] : t.b[0]);
@@ -668,7 +706,7 @@ llg_status enqueue_dm_step(llg_solver* s, const Tableau& t, const Phys& p) {
         for (int j = 0; j < st; ++j) sa.a[j] = (float)(st < S ? t.A[st][j] : t.b[j]);
         HIPCHK(s, row_inv(s, p, sa));
     }
-    HIPCHK(s, launch_ctrl_dm_accept(s->st, S, s->stream));
+    HIPCHK(s, launch_ctrl_dm_accept(s->st, S, s->progress_dev, s->stream));
     return LLG_OK;
 }
 
@@ -749,9 +787,9 @@ llg_status llg_create(int device, void* hip_stream, llg_solver** out) {
     s->user = (hipStream_t)hip_stream;
     if (hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&s->sync_ev, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&s->flag_ev[0], hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&s->flag_ev[1], hipEventDisableTiming) != hipSuccess ||
-        hipHostMalloc(&s->hflag, 2 * sizeof(int), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void**)&s->progress, sizeof(*s->progress), hipHostMallocMapped | hipHostMallocCoherent) !=
+            hipSuccess ||
+        hipHostGetDevicePointer((void**)&s->progress_dev, s->progress, 0) != hipSuccess ||
         hipMalloc(&s->st, sizeof(DevState)) != hipSuccess ||
         hipMalloc(&s->dflag, sizeof(int)) != hipSuccess) {
         llg_destroy(s);
@@ -774,9 +812,7 @@ void llg_destroy(llg_solver* s) {
     free_dev(s->st);
     free_dev(s->dflag);
     if (s->sync_ev) (void)hipEventDestroy(s->sync_ev);
-    for (auto& e : s->flag_ev)
-        if (e) (void)hipEventDestroy(e);
-    if (s->hflag) (void)hipHostFree(s->hflag);
+    if (s->progress) (void)hipHostFree(s->progress);
     if (s->stream) (void)hipStreamDestroy(s->stream);
     delete s;
 }
@@ -803,7 +839,7 @@ llg_status llg_set_geometry(llg_solver* s, int nx, int ny, int nz, int pbc_x, in
     if (nz == 1) P[2] = 1;
     const int split_y = !pb[1], split_z = nz > 1 && !pb[2];
     int Ly = split_y ? P[1] / 2 : P[1];
-    const int Lz = split_z ? P[2] / 2 : P[2];
+    int Lz = split_z ? P[2] / 2 : P[2];
     if (P[0] > kMaxPx || Ly > kMaxHalf || Lz > kMaxHalf)
         return fail(s, LLG_E_UNSUPPORTED, "FFT lengths %d x %d x %d exceed this build's limits", P[0], P[1], P[2]);
     if (P[0] % 2) return fail(s, LLG_E_UNSUPPORTED, "x FFT length must be even (periodic nx odd)");
@@ -815,6 +851,7 @@ llg_status llg_set_geometry(llg_solver* s, int nx, int ny, int nz, int pbc_x, in
     if (!generic) {
         compiled_lengths(n, pb, P);
         Ly = split_y ? P[1] / 2 : P[1];
+        Lz = split_z ? P[2] / 2 : P[2];
     }
     (void)hipStreamSynchronize(s->stream);
     free_buffers(s);
@@ -853,7 +890,8 @@ llg_status llg_set_geometry(llg_solver* s, int nx, int ny, int nz, int pbc_x, in
     s->fastrows = s->fast2d || (nz > 1 && fast2d_row_ok(P[0], g.rvar, nx == P[0]) && (nx == P[0] || 2 * nx <= P[0]) &&
                                 !generic);
     s->fast3dy = nz > 1 && fast3d_col_ok(P[1], split_y, false) && ny <= Ly && !generic;
-    s->fast3dz = nz > 1 && fast3d_col_ok(P[2], split_z, true) && nz <= Lz && !generic;
+    s->thinz = nz > 1 && fast3d_thin_ok(nz, P[2], split_z) && !generic;
+    s->fast3dz = nz > 1 && !s->thinz && fast3d_col_ok(P[2], split_z, true) && nz <= Lz && !generic;
     // x transforms above 2048 points exist only as compiled 2D row kernels
     // (the runtime-length kernels stop at 2048)
     if (P[0] > 2048 && !(s->fast2d && nz == 1))
@@ -1108,12 +1146,20 @@ llg_status llg_step(llg_solver* s, llg_method method, double dt, int64_t nsteps)
     if (p.demag_on && !s->spec_valid)
         if ((rc = launch_fwd_plain(s, 1)) != LLG_OK) return rc;
     const Tableau t = tf;
-    if (!s->gfix.exec || s->gfix.method != (int)method || s->gfix.dt != dt) {
+    int64_t left = nsteps;
+    if (nsteps >= 2 * kStepsPerGraph && (!s->gfixn.exec || s->gfixn.method != (int)method || s->gfixn.dt != dt)) {
+        if ((rc = capture(s, s->gfixn, enqueue_fixed_chunk, t, p)) != LLG_OK) return rc;
+        s->gfixn.method = (int)method;
+        s->gfixn.dt = dt;
+    }
+    if (s->gfixn.exec && s->gfixn.method == (int)method && s->gfixn.dt == dt)
+        for (; left >= kStepsPerGraph; left -= kStepsPerGraph) HIPCHK(s, hipGraphLaunch(s->gfixn.exec, s->stream));
+    if (left > 0 && (!s->gfix.exec || s->gfix.method != (int)method || s->gfix.dt != dt)) {
         if ((rc = capture(s, s->gfix, enqueue_fixed_step, t, p)) != LLG_OK) return rc;
         s->gfix.method = (int)method;
         s->gfix.dt = dt;
     }
-    for (int64_t i = 0; i < nsteps; ++i) HIPCHK(s, hipGraphLaunch(s->gfix.exec, s->stream));
+    for (; left > 0; --left) HIPCHK(s, hipGraphLaunch(s->gfix.exec, s->stream));
     if ((rc = read_state(s, &h)) != LLG_OK) return rc;
     s->spec_valid = p.demag_on != 0;
     s->k1_valid = false;
@@ -1170,7 +1216,7 @@ llg_status llg_run_dm(llg_solver* s, llg_method method, double t_end, double max
         if ((rc = capture(s, s->gdm, enqueue_dm_step, tf, p)) != LLG_OK) return rc;
         s->gdm.method = (int)method;
     }
-    if ((rc = launch_until_done(s, s->gdm.exec, -1)) != LLG_OK) return rc;
+    if ((rc = launch_until_done(s, s->gdm.exec, h.nattempt, -1)) != LLG_OK) return rc;
     if ((rc = read_state(s, &h)) != LLG_OK) return rc;
     s->spec_valid = p.demag_on != 0;
     s->k1_valid = false;
@@ -1291,7 +1337,7 @@ llg_status llg_profile_evals(llg_solver* s, int n, double* ms_out, int n_kinds, 
     if ((rc = sync(s)) != LLG_OK) return rc;
     // Every pass one compiled kernel: each kernel's own start and end
     // (events attached to its launch, as a profiler's kernel trace times it).
-    const bool exact = s->fastrows && (two_d(s) ? s->fast2d : (s->fast3dy && s->fast3dz));
+    const bool exact = s->fastrows && (two_d(s) ? s->fast2d : (s->fast3dy && (s->fast3dz || s->thinz)));
     if (exact) {
         const int np = two_d(s) ? 3 : 5;    // 2D: fwd, spectral, inv; 3D: fwd, y fwd, z, y inv, inv
         std::vector<hipEvent_t> ev(2 * (size_t)np * n + 2);
@@ -1715,7 +1761,7 @@ llg_status run_adaptive(llg_solver* s, int method, double t_end, double max_err,
         if ((rc = capture(s, s->gdp, ad.fsal ? fsal_body : plain_body, ad.t, p)) != LLG_OK) return rc;
         s->gdp.method = method;
     }
-    if ((rc = launch_until_done(s, s->gdp.exec, max_attempts > 0 ? max_attempts : -1)) != LLG_OK) return rc;
+    if ((rc = launch_until_done(s, s->gdp.exec, h.nattempt, max_attempts > 0 ? max_attempts : -1)) != LLG_OK) return rc;
     if ((rc = read_state(s, &h)) != LLG_OK) return rc;
     // the state buffers now hold the accepted solution; the x spectrum and
     // k1 buffers follow the last accepted attempt only

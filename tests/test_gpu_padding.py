@@ -24,6 +24,17 @@ FILMS = [((1, 1), (False, False)), ((3, 2), (False, False)), ((33, 2), (False, F
          ((50, 64), (False, True)), ((100, 37), (True, False))]
 
 
+# 3D: the planes of the register z pass (2 ... 8) and beyond, both sides of
+# the 16 ... 512 column lengths, every mix of periodic axes
+BLOCKS = [((20, 12, nz), (False,) * 3) for nz in (2, 3, 4, 5, 6, 7, 8, 9)] + \
+    [((100, 60, 20), (False,) * 3), ((33, 17, 24), (False,) * 3), ((6, 5, 25), (False,) * 3), ((9, 33, 48), (False,) * 3),
+     ((8, 6, 97), (False,) * 3), ((6, 97, 5), (False,) * 3), ((7, 193, 3), (False,) * 3), ((6, 300, 2), (False,) * 3),
+     ((4, 400, 3), (False,) * 3), ((70, 6, 17), (False,) * 3), ((24, 10, 3), (True, False, False)),
+     ((64, 10, 3), (True, False, False)), ((30, 24, 5), (False, True, False)), ((30, 96, 4), (False, True, False)),
+     ((40, 48, 9), (True, True, False)), ((14, 192, 2), (False, True, False)), ((20, 9, 6), (False, False, True)),
+     ((20, 18, 4), (True, True, True))]
+
+
 def maxrel(a, b):
     a = np.asarray(a, dtype=np.float64).reshape(3, -1)
     b = np.asarray(b, dtype=np.float64).reshape(3, -1)
@@ -66,6 +77,11 @@ def check(lib, monkeypatch, n, pbc):
 @pytest.mark.parametrize("n,pbc", FILMS)
 def test_films(lib, monkeypatch, n, pbc):
     check(lib, monkeypatch, (n[0], n[1], 1), (pbc[0], pbc[1], False))
+
+
+@pytest.mark.parametrize("n,pbc", BLOCKS)
+def test_blocks(lib, monkeypatch, n, pbc):
+    check(lib, monkeypatch, n, pbc)
 
 
 def test_tuning_calls_as_before(lib):
