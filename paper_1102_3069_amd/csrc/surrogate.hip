@@ -115,119 +115,150 @@ __global__ void mfma_selftest_kernel(const u16* A, const u16* B, float* C) {
 //   zg   [N][H][W][32] bf16 (may be null): data-gradient mode, a is then
 //        z times SiLU'(zg), the gradient at the previous layer's pre-activation
 // block: 4 waves, 64 pixels of `rows` consecutive rows; a wave: 16 pixels x
-// 32 channels per row, with the weight fragments of all nine taps held in
-// registers across the rows.  The bf16 tiles (a, zb, zg) pass through LDS so
-// that every lane reads or writes 16 contiguous bytes (8 channels of one
-// pixel).
+// 32 channels per row.  The weights are the A operand and the pixels the B
+// operand, so a lane's accumulators are channels of one pixel; the output
+// channels are dealt to the two accumulators (rows 4 g + i of the first:
+// channel 8 g + i, of the second: 8 g + 4 + i) so that lane group g holds
+// channels 8 g ... 8 g + 7, 16 contiguous bytes of every bf16 tensor.
+// Bound by the bytes in flight (each pixel of a layer is read and written
+// once, 192 bytes): the weight fragments sit in LDS in lane order, so that
+// five waves per SIMD fit; a row is read once, the neighbour pixels coming
+// from the neighbour lanes, and two rows ahead.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void conv_fwd_kernel(const u16* __restrict__ in, const u16* __restrict__ wt,
+// lane i of each 16 lanes takes the value of lane i - 1 (LEFT) or i + 1 of c,
+// the first (last) lane its own value of h
+template <bool LEFT>
+__device__ inline bf16x8 from_neighbour(const bf16x8& c, const bf16x8& h) {
+    int cw[4], hw[4];
+    memcpy(cw, &c, 16);
+    memcpy(hw, &h, 16);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        hw[i] = LEFT ? __builtin_amdgcn_update_dpp(hw[i], cw[i], 0x111, 0xf, 0xf, false)
+                     : __builtin_amdgcn_update_dpp(hw[i], cw[i], 0x101, 0xf, 0xf, false);
+    bf16x8 r;
+    memcpy(&r, hw, 16);
+    return r;
+}
+
+__device__ inline uint32_t pack2(float lo, float hi) { return (uint32_t)f2bf_hw(lo) | (uint32_t)f2bf_hw(hi) << 16; }
+
+__global__ __launch_bounds__(256, 5) void conv_fwd_kernel(const u16* __restrict__ in, const u16* __restrict__ wt,
                                                        const float* __restrict__ bias, float* __restrict__ z,
                                                        float* __restrict__ zc, u16* __restrict__ zb, u16* __restrict__ a,
                                                        const u16* __restrict__ zg, int H, int W, int act, int rows) {
-    __shared__ u16 ws[9 * CH * CH];
-    __shared__ u16 tile[4][2][16 * CH];   // per wave: [0] a, [1] zb or zg; [pixel][channel]
+    __shared__ uint4 wsh[18 * 64];   // [tap][accumulator][lane]
     const int tid = threadIdx.x;
-    for (int i = tid; i < 9 * CH * CH / 8; i += 256)
-        reinterpret_cast<uint4*>(ws)[i] = reinterpret_cast<const uint4*>(wt)[i];
-    __syncthreads();
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = blockIdx.z;
     const int x0 = blockIdx.x * 64 + wave * 16;
     const int col = lane % 16, kg = lane / 16;
     const size_t img = (size_t)n * H * W;
-    u16* ta = tile[wave][0];
-    u16* tz = tile[wave][1];
-    // the lane's 16-byte chunk of a tile row: pixel lane / 4, channels 8 (lane % 4)
-    const int cpx = lane >> 2, cch = 8 * (lane & 3);
-    bf16x8 B0[9], B1[9];
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-        B0[t] = load8(ws + t * CH * CH + col * CH + 8 * kg);
-        B1[t] = load8(ws + t * CH * CH + (16 + col) * CH + 8 * kg);
-    }
-    const float bias0 = bias ? bias[col] : 0.f, bias1 = bias ? bias[16 + col] : 0.f;
     const int ya = blockIdx.y * rows, yb = min(ya + rows, H);
-    // the A fragments of input rows y-1, y, y+1 (taps v = 0, 1, 2) roll down
-    // the rows; the next input row is read while this row's epilogue runs.
-    // Every lane reads (outside the image: the nearest pixel inside), so that
-    // no load is conditional and the waits stay exact; a row's fragments
-    // outside the image are zeroed in place once they have arrived.
-    auto load_row = [&](int yy, bf16x8 (&dst)[3]) {
-        const int yc = min(max(yy, 0), H - 1);
-#pragma unroll
-        for (int v = 0; v < 3; ++v) {
-            const int xc = min(max(x0 + col + v - 1, 0), W - 1);
-            dst[v] = load8(in + ((img + (size_t)yc * W + xc) * CH + 8 * kg));
-        }
+    const int x = x0 + col;
+    const bool xin = x < W;
+    const int xs = min(x, W - 1);
+    // the raw fragments of a row: the lane's pixel, and for the first and
+    // last lane of 16 the pixel beyond.  Every lane reads (outside the image:
+    // the nearest pixel inside), so that no load is conditional and the waits
+    // stay exact; what lies outside is zeroed once it has arrived.
+    struct Raw {
+        bf16x8 c, h;
     };
-    auto mask_row = [&](int yy, bf16x8 (&r)[3]) {
-#pragma unroll
-        for (int v = 0; v < 3; ++v) {
-            const int xx = x0 + col + v - 1;
-            if (!(yy >= 0 && yy < H && xx >= 0 && xx < W)) r[v] = zero8();
-        }
+    const int hx = col == 0 ? x0 - 1 : col == 15 ? x0 + 16 : x;
+    const bool hin = hx >= 0 && hx < W;
+    const int co = xs * CH + 8 * kg, ho = min(max(hx, 0), W - 1) * CH + 8 * kg;
+    const bool inside = x0 >= 1 && x0 + 16 < W;   // no pixel of this wave's rows outside the image
+    auto load_row = [&](int yy, Raw& r) {
+        const u16* src = in + (img + (size_t)min(max(yy, 0), H - 1) * W) * CH;
+        r.c = load8(src + co);
+        r.h = load8(src + ho);
     };
-    bf16x8 Ar[3][3];
-    load_row(ya - 1, Ar[0]);
-    load_row(ya, Ar[1]);
-    load_row(ya + 1, Ar[2]);
-    mask_row(ya - 1, Ar[0]);
-    mask_row(ya, Ar[1]);
-    for (int y = ya; y < yb; ++y) {
-        mask_row(y + 1, Ar[2]);
+    // the fragments of taps v = 0, 1, 2
+    auto expand = [&](int yy, Raw r, bf16x8 (&f)[3]) {
+        const bool row = yy >= 0 && yy < H;
+        if (!(row && inside)) {
+            if (!(row && xin)) r.c = zero8();
+            if (!(row && hin)) r.h = zero8();
+        }
+        f[0] = from_neighbour<true>(r.c, r.h);
+        f[1] = r.c;
+        f[2] = from_neighbour<false>(r.c, r.h);
+    };
+    Raw Ra, Rb, T0, T1;
+    load_row(ya - 1, Ra);
+    load_row(ya, Rb);
+    load_row(ya + 1, T0);
+    load_row(ya + 2, T1);
+    for (int i = tid; i < 18 * 64; i += 256) {
+        const int f = i >> 6, l = i & 63;      // lane l's weights of tap f / 2, accumulator f % 2
+        const int c = l % 16, k = l / 16;
+        const int ch = 8 * (c >> 2) + (c & 3) + 4 * (f & 1);
+        wsh[i] = *reinterpret_cast<const uint4*>(wt + ((f >> 1) * CH + ch) * CH + 8 * k);
+    }
+    float bs[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) bs[i] = bias ? bias[8 * kg + i] : 0.f;
+    __syncthreads();
+    bf16x8 F0[3], F1[3], F2[3];
+    expand(ya - 1, Ra, F0);
+    expand(ya, Rb, F1);
+    const u16* wl = reinterpret_cast<const u16*>(wsh + lane);
+    // one output row from input rows y-1, y, y+1: P and Q expanded, y + 1 raw
+    // in T, expanded into R; row y + 3 goes into T
+    auto step = [&](int y, bf16x8 (&P)[3], bf16x8 (&Q)[3], bf16x8 (&R)[3], Raw& T) {
+        expand(y + 1, T, R);
+        if (y + 3 <= yb) load_row(y + 3, T);
         f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
 #pragma unroll
-        for (int u = 0; u < 3; ++u) {
+        for (int t = 0; t < 9; ++t) {
+            const bf16x8 w0 = load8(wl + (2 * t) * 512), w1 = load8(wl + (2 * t + 1) * 512);
+            const bf16x8 b = t < 3 ? P[t] : t < 6 ? Q[t - 3] : R[t - 6];
+            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w0, b, acc0, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, b, acc1, 0, 0, 0);
+        }
+        const size_t px = img + (size_t)y * W;
+        const size_t o = (px + xs) * CH + 8 * kg;   // the lane's eight channels
+        uint4 g = make_uint4(0, 0, 0, 0);
+        if (zg) g = *reinterpret_cast<const uint4*>(zg + o);
+        float zv[8];
 #pragma unroll
-            for (int v = 0; v < 3; ++v) {
-                acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ar[u][v], B0[u * 3 + v], acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ar[u][v], B1[u * 3 + v], acc1, 0, 0, 0);
-            }
+        for (int i = 0; i < 4; ++i) {
+            zv[i] = acc0[i] + bs[i];
+            zv[4 + i] = acc1[i] + bs[4 + i];
         }
-        const size_t crow = (img + (size_t)y * W + x0 + cpx) * CH + cch;   // the lane's chunk in global memory
-        const bool cin = x0 + cpx < W;
-        uint4 gch = make_uint4(0, 0, 0, 0);
-        if (zg) gch = *reinterpret_cast<const uint4*>(zg + (img + (size_t)y * W + min(x0 + cpx, W - 1)) * CH + cch);
+        float ov[8];
+        if (zg) {
+            const uint32_t gw[4] = {g.x, g.y, g.z, g.w};
 #pragma unroll
-        for (int v = 0; v < 3; ++v) {
-            Ar[0][v] = Ar[1][v];
-            Ar[1][v] = Ar[2][v];
-        }
-        load_row(y + 1 < yb ? y + 2 : H, Ar[2]);   // (row H: zeros, nothing read)
-        if (zg) *reinterpret_cast<uint4*>(tz + cpx * CH + cch) = gch;
-        __builtin_amdgcn_wave_barrier();
-        // C layout: lane holds channels col and 16 + col of pixel 4 kg + r
+            for (int i = 0; i < 8; ++i) {
+                const float zz = __uint_as_float(i & 1 ? gw[i >> 1] & 0xffff0000u : gw[i >> 1] << 16);
+                ov[i] = zv[i] * silu_grad(zz);
+            }
+        } else {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int px = 4 * kg + r;
-            const float v0 = acc0[r] + bias0, v1 = acc1[r] + bias1;
-            if (z && x0 + px < W) {
-                const size_t p = (img + (size_t)y * W + x0 + px) * CH;
-                z[p + col] = v0;
-                z[p + 16 + col] = v1;
-            }
-            if (zc && col < KC && x0 + px < W) zc[(img + (size_t)y * W + x0 + px) * KC + col] = v0;
-            float o0 = v0, o1 = v1;
-            if (zg) {
-                o0 *= silu_grad(bf2f(tz[px * CH + col]));
-                o1 *= silu_grad(bf2f(tz[px * CH + 16 + col]));
-            } else if (act) {
-                o0 = silu(v0);
-                o1 = silu(v1);
-            }
-            ta[px * CH + col] = f2bf_hw(o0);
-            ta[px * CH + 16 + col] = f2bf_hw(o1);
-            if (zb) {
-                tz[px * CH + col] = f2bf_hw(v0);
-                tz[px * CH + 16 + col] = f2bf_hw(v1);
-            }
+            for (int i = 0; i < 8; ++i) ov[i] = act ? silu(zv[i]) : zv[i];
         }
-        __builtin_amdgcn_wave_barrier();
-        if (cin) {
-            if (a) *reinterpret_cast<uint4*>(a + crow) = *reinterpret_cast<const uint4*>(ta + cpx * CH + cch);
-            if (zb) *reinterpret_cast<uint4*>(zb + crow) = *reinterpret_cast<const uint4*>(tz + cpx * CH + cch);
+        if (!xin) return;
+        if (z) {
+            *reinterpret_cast<float4*>(z + o) = make_float4(zv[0], zv[1], zv[2], zv[3]);
+            *reinterpret_cast<float4*>(z + o + 4) = make_float4(zv[4], zv[5], zv[6], zv[7]);
         }
-        __builtin_amdgcn_wave_barrier();
+        if (zc && kg == 0) *reinterpret_cast<float4*>(zc + (px + xs) * KC) = make_float4(zv[0], zv[1], zv[2], zv[3]);
+        if (a)
+            *reinterpret_cast<uint4*>(a + o) =
+                make_uint4(pack2(ov[0], ov[1]), pack2(ov[2], ov[3]), pack2(ov[4], ov[5]), pack2(ov[6], ov[7]));
+        if (zb)
+            *reinterpret_cast<uint4*>(zb + o) =
+                make_uint4(pack2(zv[0], zv[1]), pack2(zv[2], zv[3]), pack2(zv[4], zv[5]), pack2(zv[6], zv[7]));
+    };
+    for (int y = ya; y < yb; y += 6) {
+        step(y, F0, F1, F2, T0);
+        if (y + 1 < yb) step(y + 1, F1, F2, F0, T1);
+        if (y + 2 < yb) step(y + 2, F2, F0, F1, T0);
+        if (y + 3 < yb) step(y + 3, F0, F1, F2, T1);
+        if (y + 4 < yb) step(y + 4, F1, F2, F0, T0);
+        if (y + 5 < yb) step(y + 5, F2, F0, F1, T1);
     }
 }
 
@@ -653,11 +684,13 @@ int wg_blocks(const llg_sur* s, int N) {
 }
 
 // convolution rows per forward block: blocks of 64 pixels by `rows` rows,
-// about 2048 of them, at most 16 rows
+// as many rows (at most 24) as let whole rounds of five blocks per compute
+// unit cover the image (a partly filled last round costs a whole one)
 void launch_conv(llg_sur* s, const u16* in, const u16* wt, const float* bias, float* z, float* zc, u16* zb, u16* a,
                  const u16* zg, int N, int act) {
-    const long long rb = (long long)((s->W + 63) / 64) * s->H * N;
-    const int rows = (int)std::min<long long>(16, std::max<long long>(1, rb / 2048));
+    const long long rb = (long long)((s->W + 63) / 64) * s->H * N, round = 5 * 256;
+    const long long rounds = (rb + round * 24 - 1) / (round * 24);
+    const int rows = (int)((rb + round * rounds - 1) / (round * rounds));
     hipLaunchKernelGGL(conv_fwd_kernel, dim3((s->W + 63) / 64, (s->H + rows - 1) / rows, N), dim3(256), 0,
                        s->stream, in, wt, bias, z, zc, zb, a, zg, s->H, s->W, act, rows);
 }
