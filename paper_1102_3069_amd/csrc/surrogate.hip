@@ -265,72 +265,51 @@ __global__ __launch_bounds__(256, 5) void conv_fwd_kernel(const u16* __restrict_
 // ---------------------------------------------------------------------------
 // weight gradient: dW[u][v][co][ci] = sum over pixels p of gz[p][co] times
 // a_in[p + (u - 1, v - 1)][ci], db[co] = sum_p gz[p][co].  Summed over the
-// input pixel q = p + (u - 1, v - 1) instead, the input is staged unshifted
-// and the gradient row in three horizontally shifted copies, so every MFMA
-// fragment is one aligned 16-byte LDS read.  A block owns 64 input columns
-// of `rows` consecutive gradient rows; the three input rows a gradient row
-// pairs with rotate through a ring in LDS, so each input row is staged
-// once.  Staging transposes channels-last data to [channel][pixel] in
-// registers (4 pixels x 8 channels per thread).  Wave w accumulates the
-// input-channel half 16 (w & 1) and the pixel half 32 (w >> 1) of every
-// tap; the two pixel halves are added in LDS at the end in a fixed order
-// and the block writes one partial sum, reduced by the two reduce kernels.
+// input pixel q = p + (u - 1, v - 1) instead, so that the input fragments are
+// aligned.  Staging transposes channels-last rows to [channel][pixel] in LDS
+// (2 pixels x 8 channels per thread); a gradient row is staged once, with one
+// pixel beyond either end, and its fragments shifted by one pixel are made of
+// two neighbouring words in registers.  A block owns 64 input columns of
+// `rows` consecutive gradient rows; the input rows rotate through a ring of
+// four and the gradient rows through two buffers, so one barrier per row
+// separates staging row y + 1 from the MFMAs of row y; the reads run two rows
+// ahead.  Wave w accumulates the input-channel half 16 (w & 1) and the pixel
+// half 32 (w >> 1) of every tap; the two pixel halves are added in LDS at the
+// end in a fixed order and the block writes one partial sum, reduced by the
+// reduce kernels.
 // ---------------------------------------------------------------------------
-constexpr int WG_LD = 72;          // LDS row stride (u16): 64 pixels + 8, rows 16-byte aligned
-constexpr int WG_TARGET = 1024;    // blocks a weight-gradient launch aims for
+constexpr int WG_LA = 72;          // LDS row strides (u16), 16-byte aligned rows on distinct banks: input 64 + 8,
+constexpr int WG_LG = 88;          // gradient 8 (the last one the pixel before) + 64 + 16 (the first the pixel after)
+constexpr int WG_ROUND = 3 * 256;  // blocks the card holds at a time
 constexpr int WG_SEG = 64;         // segments of the first reduction stage
 constexpr int NWG = 9 * CH * CH;   // weight-gradient entries of one layer
 
-// pixels xs + 4 q .. xs + 4 q + 3 of row y, channels 8 cg .. 8 cg + 7, into
-// dst[channel][4 q + i] (zero outside the image), in two halves: the reads
-// into registers, then the transposed LDS stores
-__device__ inline void load_quad(uint4 (&v)[4], const u16* __restrict__ src, size_t img, int H, int W, int y, int xs,
-                                 int q, int cg) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int x = xs + 4 * q + i;
-        v[i] = make_uint4(0, 0, 0, 0);
-        if (y >= 0 && y < H && x >= 0 && x < W)
-            v[i] = *reinterpret_cast<const uint4*>(src + (img + (size_t)y * W + x) * CH + 8 * cg);
-    }
+// channels 8 cg .. 8 cg + 7 of pixel x of row y (zero outside the image)
+__device__ inline uint4 load_px(const u16* __restrict__ src, size_t img, int H, int W, int y, int x, int cg) {
+    if (y < 0 || y >= H || x < 0 || x >= W) return make_uint4(0, 0, 0, 0);
+    return *reinterpret_cast<const uint4*>(src + (img + (size_t)y * W + x) * CH + 8 * cg);
 }
-__device__ inline void store_quad(u16* dst, const uint4 (&v)[4], int q, int cg) {
-    unsigned w[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        w[i][0] = v[i].x;
-        w[i][1] = v[i].y;
-        w[i][2] = v[i].z;
-        w[i][3] = v[i].w;
-    }
+// two pixels to dst[channel][pixel] (row stride ld, even place)
+__device__ inline void store_pair(u16* dst, int ld, const uint4 (&v)[2], int cg) {
+    const uint32_t a[4] = {v[0].x, v[0].y, v[0].z, v[0].w}, b[4] = {v[1].x, v[1].y, v[1].z, v[1].w};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         // word k of a pixel holds channels 2k (low half) and 2k + 1 (high half)
-        uint2 lo, hi;
-        lo.x = (w[0][k] & 0xffffu) | (w[1][k] << 16);
-        lo.y = (w[2][k] & 0xffffu) | (w[3][k] << 16);
-        hi.x = (w[0][k] >> 16) | (w[1][k] & 0xffff0000u);
-        hi.y = (w[2][k] >> 16) | (w[3][k] & 0xffff0000u);
-        *reinterpret_cast<uint2*>(dst + (8 * cg + 2 * k) * WG_LD + 4 * q) = lo;
-        *reinterpret_cast<uint2*>(dst + (8 * cg + 2 * k + 1) * WG_LD + 4 * q) = hi;
+        *reinterpret_cast<uint32_t*>(dst + (8 * cg + 2 * k) * ld) = (a[k] & 0xffffu) | (b[k] << 16);
+        *reinterpret_cast<uint32_t*>(dst + (8 * cg + 2 * k + 1) * ld) = (a[k] >> 16) | (b[k] & 0xffff0000u);
     }
 }
-__device__ inline void stage_quad(u16* dst, const u16* __restrict__ src, size_t img, int H, int W, int y, int xs,
-                                  int q, int cg) {
-    uint4 v[4];
-    load_quad(v, src, img, H, W, y, xs, q, cg);
-    store_quad(dst, v, q, cg);
-}
 
-__global__ __launch_bounds__(256) void conv_wgrad_kernel(const u16* __restrict__ gz, const u16* __restrict__ ain,
-                                                         float* __restrict__ part_w, float* __restrict__ part_b,
-                                                         int H, int W, int rows) {
-    // staging: gradient gT[3 shifts][32][72] and input aT[3 ring slots][32][72]
-    // (27 KB); at the end the same memory holds the pixel-half exchange (36 KB)
+__global__ __launch_bounds__(256, 3) void conv_wgrad_kernel(const u16* __restrict__ gz, const u16* __restrict__ ain,
+                                                            float* __restrict__ part_w, float* __restrict__ part_b,
+                                                            int H, int W, int rows) {
+    // staging: gradient gT[2 buffers][32][88] and input aT[4 ring slots][32][72]
+    // (29 KB); at the end the same memory holds the pixel-half exchange (36 KB)
     __shared__ __align__(16) unsigned char smem[2 * 72 * 64 * 4];
+    __shared__ float bsum[2][CH];
     u16* gT = reinterpret_cast<u16*>(smem);
-    u16* aT = gT + 3 * CH * WG_LD;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    u16* aT = gT + 2 * CH * WG_LG;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane % 16, kg = lane / 16;
     const int cih = wave & 1, kh = wave >> 1;
     const int n = blockIdx.z, x0 = blockIdx.x * 64;
@@ -339,41 +318,86 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(const u16* __restrict__
     f32x4 acc[18];
 #pragma unroll
     for (int i = 0; i < 18; ++i) acc[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    float bpart = 0.f;   // channel tid / 8, pixels 8 (tid % 8) ..
-    // input rows ya - 1 and ya into their ring slots ((row + 3) mod 3)
-    if (tid < 128) {
-        const int r = ya - 1 + tid / 64;
-        stage_quad(aT + ((r + 3) % 3) * CH * WG_LD, ain, img, H, W, r, x0, (tid / 4) % 16, tid % 4);
-    }
-    // per row y: gT[v][co][px] = gz[y][x0 + px + 1 - v] (threads < 192) and
-    // input row y + 1 into its ring slot (the others); the reads of the next
-    // row's share go out before this row's MFMAs
-    auto load_share = [&](int y, uint4 (&v)[4]) {
-        if (tid < 192) load_quad(v, gz, img, H, W, y, x0 + 1 - tid / 64, (tid / 4) % 16, tid % 4);
-        else load_quad(v, ain, img, H, W, y + 1, x0, (tid - 192) / 4, (tid - 192) % 4);
-    };
-    uint4 share[4];
-    load_share(ya, share);
-    for (int y = ya; y < yb; ++y) {
-        __syncthreads();
-        if (tid < 192) store_quad(gT + (tid / 64) * CH * WG_LD, share, (tid / 4) % 16, tid % 4);
-        else store_quad(aT + ((y + 1) % 3) * CH * WG_LD, share, (tid - 192) / 4, (tid - 192) % 4);
-        __syncthreads();
-        if (y + 1 < yb) load_share(y + 1, share);
-        {
-            const u16* g1 = gT + CH * WG_LD + (tid >> 3) * WG_LD + 8 * (tid & 7);
+    float bp[8];         // gradient threads: sums of channels 8 cg ..
 #pragma unroll
-            for (int i = 0; i < 8; ++i) bpart += bf2f(g1[i]);
+    for (int i = 0; i < 8; ++i) bp[i] = 0.f;
+    // threads of waves 0, 1 stage the gradient row, those of waves 2, 3 the
+    // input row below it; the first eight threads also the two pixels beyond
+    const bool grad = wave < 2;
+    const int q = (tid >> 2) & 31, cg = tid & 3;
+    struct Share {
+        uint4 v[2], h;
+    };
+    auto load_share = [&](int y, Share& s) {     // gradient row y, input row y + 1
+        const u16* src = grad ? gz : ain;
+        const int yy = grad ? y : y + 1;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) s.v[i] = load_px(src, img, H, W, yy, x0 + 2 * q + i, cg);
+        if (tid < 8) s.h = load_px(gz, img, H, W, y, tid < 4 ? x0 - 1 : x0 + 64, cg);
+    };
+    auto store_share = [&](int y, const Share& s) {
+        if (grad) {
+            u16* g = gT + (y & 1) * CH * WG_LG;
+            store_pair(g + 8 + 2 * q, WG_LG, s.v, cg);
+            const uint32_t w[2][4] = {{s.v[0].x, s.v[0].y, s.v[0].z, s.v[0].w}, {s.v[1].x, s.v[1].y, s.v[1].z, s.v[1].w}};
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    bp[2 * k] += __uint_as_float(w[i][k] << 16);
+                    bp[2 * k + 1] += __uint_as_float(w[i][k] & 0xffff0000u);
+                }
+            if (tid < 8) {
+                const uint32_t h[4] = {s.h.x, s.h.y, s.h.z, s.h.w};
+                u16* d = g + (tid < 4 ? 7 : 72) + 8 * cg * WG_LG;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    d[2 * k * WG_LG] = (u16)(h[k] & 0xffffu);
+                    d[(2 * k + 1) * WG_LG] = (u16)(h[k] >> 16);
+                }
+            }
+        } else {
+            store_pair(aT + ((y + 1) & 3) * CH * WG_LA + 2 * q, WG_LA, s.v, cg);
         }
-        const int kc = 32 * kh + 8 * kg;
+    };
+    Share s0, s1;
+    {
+        // input rows ya - 1 and ya into their ring slots (row mod 4)
+        uint4 v[2];
+        const int r = grad ? ya - 1 : ya;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) v[i] = load_px(ain, img, H, W, r, x0 + 2 * q + i, cg);
+        load_share(ya, s0);
+        if (ya + 1 < yb) load_share(ya + 1, s1);
+        store_pair(aT + (r & 3) * CH * WG_LA + 2 * q, WG_LA, v, cg);
+    }
+    store_share(ya, s0);
+    if (ya + 2 < yb) load_share(ya + 2, s0);
+    __syncthreads();
+    const int kc = 32 * kh + 8 * kg;
+    // the MFMAs of row y, after the staging of row y + 1 (held in s, which
+    // takes row y + 3)
+    auto step = [&](int y, Share& s) {
+        if (y + 1 < yb) store_share(y + 1, s);
+        if (y + 3 < yb) load_share(y + 3, s);
         bf16x8 Bu[3];
 #pragma unroll
-        for (int u = 0; u < 3; ++u) Bu[u] = load8(aT + ((y + u + 2) % 3) * CH * WG_LD + (16 * cih + col) * WG_LD + kc);
+        for (int u = 0; u < 3; ++u) Bu[u] = load8(aT + ((y + u - 1) & 3) * CH * WG_LA + (16 * cih + col) * WG_LA + kc);
 #pragma unroll
-        for (int v = 0; v < 3; ++v) {
+        for (int coh = 0; coh < 2; ++coh) {
+            const u16* g = gT + (y & 1) * CH * WG_LG + (16 * coh + col) * WG_LG + 8 + kc;
+            const uint4 d = *reinterpret_cast<const uint4*>(g);
+            const uint32_t before = *reinterpret_cast<const uint32_t*>(g - 2);
+            const uint32_t after = *reinterpret_cast<const uint32_t*>(g + 8);
+            // pixels one to the right (v = 0), in place, one to the left (v = 2)
+            const uint32_t m = __builtin_amdgcn_alignbit(d.x, before, 16), a0 = __builtin_amdgcn_alignbit(d.y, d.x, 16),
+                           a1 = __builtin_amdgcn_alignbit(d.z, d.y, 16), a2 = __builtin_amdgcn_alignbit(d.w, d.z, 16),
+                           a3 = __builtin_amdgcn_alignbit(after, d.w, 16);
+            const uint4 f[3] = {make_uint4(a0, a1, a2, a3), d, make_uint4(m, a0, a1, a2)};
 #pragma unroll
-            for (int coh = 0; coh < 2; ++coh) {
-                const bf16x8 A = load8(gT + v * CH * WG_LD + (16 * coh + col) * WG_LD + kc);
+            for (int v = 0; v < 3; ++v) {
+                bf16x8 A;
+                memcpy(&A, &f[v], 16);
 #pragma unroll
                 for (int u = 0; u < 3; ++u) {
                     f32x4& c = acc[(u * 3 + v) * 2 + coh];
@@ -381,15 +405,27 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(const u16* __restrict__
                 }
             }
         }
+        __syncthreads();
+    };
+    for (int y = ya; y < yb; y += 2) {
+        step(y, s1);
+        if (y + 1 < yb) step(y + 1, s0);
     }
     // add the pixel halves: waves 2, 3 hand their sums to waves 0, 1
-    __syncthreads();
     float* red = reinterpret_cast<float*>(smem);
     if (kh == 1) {
 #pragma unroll
         for (int i = 0; i < 18; ++i)
 #pragma unroll
             for (int r = 0; r < 4; ++r) red[(cih * 72 + 4 * i + r) * 64 + lane] = acc[i][r];
+    } else {
+        // (waves 0 and 1 hold the gradient rows' sums) over the pixel pairs
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            float b = bp[i];
+            for (int off = 32; off >= 4; off >>= 1) b += __shfl_xor(b, off);
+            if (lane < 4) bsum[wave][8 * lane + i] = b;
+        }
     }
     __syncthreads();
     const int blk = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
@@ -405,18 +441,27 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(const u16* __restrict__
             }
         }
     }
-    bpart += __shfl_xor(bpart, 4);
-    bpart += __shfl_xor(bpart, 2);
-    bpart += __shfl_xor(bpart, 1);
-    if ((tid & 7) == 0) part_b[(size_t)blk * CH + (tid >> 3)] = bpart;
+    if (tid < CH) part_b[(size_t)blk * CH + tid] = bsum[0][tid] + bsum[1][tid];
 }
 
+// the layers of a launch over several of them (blockIdx.z)
+struct LayerSet {
+    int cin[NL], cout[NL];
+    float *w[NL], *b[NL];            // weights [cout][cin][3][3] and biases (or their gradients)
+    const float *gw[NL], *gb[NL];    // gradients (Adam)
+    float *m1w[NL], *m1b[NL], *m2w[NL], *m2b[NL];
+    u16 *wf[NL], *wtr[NL];           // bf16 forward and data-gradient weights
+};
+
 // first stage of the deterministic reduction: entry i (weights, then the 32
-// bias entries) summed over segment blockIdx.y of the block partials, in
-// block order
+// bias entries) of a layer summed over segment blockIdx.y of the block
+// partials, in block order
 __global__ void wgrad_reduce1_kernel(const float* part_w, const float* part_b, int nblk, float* part2) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= NWG + CH) return;
+    part_w += (size_t)blockIdx.z * nblk * NWG;
+    part_b += (size_t)blockIdx.z * nblk * CH;
+    part2 += (size_t)blockIdx.z * gridDim.y * (NWG + CH);
     const int per = (nblk + gridDim.y - 1) / gridDim.y;
     const int b0 = blockIdx.y * per, b1 = min(nblk, b0 + per);
     float s = 0.f;
@@ -430,17 +475,21 @@ __global__ void wgrad_reduce1_kernel(const float* part_w, const float* part_b, i
     part2[(size_t)blockIdx.y * (NWG + CH) + i] = s;
 }
 
-// second stage: the segments in order
-__global__ void wgrad_reduce2_kernel(const float* part2, int nseg, float* gw, float* gb) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// second stage: the segments in order, into the parameter layout
+__global__ void wgrad_reduce2_kernel(const float* part2, int nseg, LayerSet ls) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, l = blockIdx.z;
     if (i >= NWG + CH) return;
+    part2 += (size_t)l * nseg * (NWG + CH);
     float s = 0.f;
 #pragma unroll 8
     for (int k = 0; k < nseg; ++k) s += part2[(size_t)k * (NWG + CH) + i];
-    if (i < NWG)
-        gw[i] = s;
-    else
-        gb[i - NWG] = s;
+    const int cin = ls.cin[l], cout = ls.cout[l];
+    if (i < NWG) {
+        const int tap = i / (CH * CH), co = (i / CH) % CH, ci = i % CH;
+        if (co < cout && ci < cin) ls.w[l][(co * cin + ci) * 9 + tap] = s;
+    } else if (i - NWG < cout) {
+        ls.b[l][i - NWG] = s;
+    }
 }
 
 // gz = g * silu'(z) (hidden layers) or g (last layer), as bf16
@@ -451,65 +500,74 @@ __global__ void act_bwd_kernel(const float* g, const float* z, u16* gz, size_t n
     gz[i] = f2bf(v);
 }
 
-// x = (m, B / 50 mT, 0...) bf16 channels-last; m is [n][3][H][W] float
-__global__ void make_input_kernel(const float* m, const float* B, u16* x, int N, int H, int W) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t npx = (size_t)N * H * W;
-    if (i >= npx) return;
-    const int n = (int)(i / ((size_t)H * W));
-    const size_t p = i - (size_t)n * H * W;
-    // m as a BF16 pair: hi = bf16(m), lo = bf16(256 (m - hi)) (m - hi is
-    // exact in FP32), so the first layer sees m to about 16 bits
-    uint32_t ch[9];
-    for (int c = 0; c < 3; ++c) {
-        const float v = m[((size_t)n * 3 + c) * H * W + p];
-        const u16 hi = f2bf(v);
-        ch[c] = hi;
-        ch[3 + c] = f2bf((v - bf2f(hi)) * LO_SCALE);
+// the 32 channels of the block's 256 pixels (first pixel p0 of npx) from
+// the first NQ 16-byte quarters in LDS, the rest zero, so that consecutive
+// lanes write consecutive 16 bytes
+template <int NQ>
+__device__ inline void write_pixels(u16* x, size_t p0, size_t npx, const uint4 (*q)[256]) {
+    uint4* xo = reinterpret_cast<uint4*>(x) + 4 * p0;
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+        const int i = it * 256 + (int)threadIdx.x, px = i >> 2, k = i & 3;
+        if (p0 + px < npx) xo[i] = k < NQ ? q[k < NQ ? k : 0][px] : make_uint4(0u, 0u, 0u, 0u);
     }
-    for (int c = 0; c < 3; ++c) ch[6 + c] = f2bf(B[n * 3 + c] / B_SCALE);
-    // the pixel's 32 channels as four 16-byte stores (channels 9.. zero)
-    uint4* xo = reinterpret_cast<uint4*>(x + i * CH);
-    xo[0] = make_uint4(ch[0] | ch[1] << 16, ch[2] | ch[3] << 16, ch[4] | ch[5] << 16, ch[6] | ch[7] << 16);
-    xo[1] = make_uint4(ch[8], 0u, 0u, 0u);
-    xo[2] = make_uint4(0u, 0u, 0u, 0u);
-    xo[3] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// x = (m, B / 50 mT, 0...) bf16 channels-last; m is [n][3][H][W] float,
+// hw = H W; blockIdx.y: the state
+__global__ __launch_bounds__(256) void make_input_kernel(const float* m, const float* B, u16* x, int hw) {
+    __shared__ uint4 q[2][256];
+    const int n = blockIdx.y;
+    const size_t p0 = (size_t)blockIdx.x * 256, p = p0 + threadIdx.x;
+    if (p < (size_t)hw) {
+        // m as a BF16 pair: hi = bf16(m), lo = bf16(256 (m - hi)) (m - hi is
+        // exact in FP32), so the first layer sees m to about 16 bits
+        uint32_t ch[9];
+        for (int c = 0; c < 3; ++c) {
+            const float v = m[((size_t)n * 3 + c) * hw + p];
+            const u16 hi = f2bf(v);
+            ch[c] = hi;
+            ch[3 + c] = f2bf((v - bf2f(hi)) * LO_SCALE);
+        }
+        for (int c = 0; c < 3; ++c) ch[6 + c] = f2bf(B[n * 3 + c] / B_SCALE);
+        q[0][threadIdx.x] = make_uint4(ch[0] | ch[1] << 16, ch[2] | ch[3] << 16, ch[4] | ch[5] << 16, ch[6] | ch[7] << 16);
+        q[1][threadIdx.x] = make_uint4(ch[8], 0u, 0u, 0u);
+    }
+    __syncthreads();
+    write_pixels<2>(x + (size_t)n * hw * CH, p0, hw, q);
 }
 
 // loss gradient (bf16: the gradient at the last layer's pre-activation) of
 // the mean squared error of the network output against
-// (m_target - base) / scale, and per-block loss partials
-__global__ void loss_kernel(const float* zout, const float* base, const float* mt, u16* gz, float* part, int N,
-                            int H, int W, float inv_scale) {
+// (m_target - base) / scale, and per-block loss partials; blockIdx.y: the state
+__global__ __launch_bounds__(256) void loss_kernel(const float* zout, const float* base, const float* mt, u16* gz,
+                                                   float* part, int hw, float inv_scale) {
     __shared__ float red[256];
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t npx = (size_t)N * H * W;
-    const float inv = 1.0f / (3.0f * (float)npx);
+    __shared__ uint4 q[1][256];
+    const int n = blockIdx.y;
+    const size_t p0 = (size_t)blockIdx.x * 256, p = p0 + threadIdx.x;
+    const float inv = 1.0f / (3.0f * (float)((size_t)gridDim.y * hw));
     float l = 0.f;
-    if (i < npx) {
-        const int n = (int)(i / ((size_t)H * W));
-        const size_t p = i - (size_t)n * H * W;
+    if (p < (size_t)hw) {
+        const float4 zo = *reinterpret_cast<const float4*>(zout + ((size_t)n * hw + p) * KC);
+        const float zv[3] = {zo.x, zo.y, zo.z};
         uint32_t gb[3];
         for (int c = 0; c < 3; ++c) {
-            const size_t q = ((size_t)n * 3 + c) * H * W + p;
-            const float d = zout[i * KC + c] - (mt[q] - base[q]) * inv_scale;
+            const size_t i = ((size_t)n * 3 + c) * hw + p;
+            const float d = zv[c] - (mt[i] - base[i]) * inv_scale;
             l += d * d;
             gb[c] = f2bf(2.0f * d * inv);
         }
-        // the pixel's 32 gradient channels (3.. zero) as four 16-byte stores
-        uint4* go = reinterpret_cast<uint4*>(gz + i * CH);
-        go[0] = make_uint4(gb[0] | gb[1] << 16, gb[2], 0u, 0u);
-        go[1] = make_uint4(0u, 0u, 0u, 0u);
-        go[2] = make_uint4(0u, 0u, 0u, 0u);
-        go[3] = make_uint4(0u, 0u, 0u, 0u);
+        q[0][threadIdx.x] = make_uint4(gb[0] | gb[1] << 16, gb[2], 0u, 0u);
     }
     red[threadIdx.x] = l;
     __syncthreads();
+    write_pixels<1>(gz + (size_t)n * hw * CH, p0, hw, q);
     for (int s = 128; s > 0; s >>= 1) {
         if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
         __syncthreads();
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0] * inv;
+    if (threadIdx.x == 0) part[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = red[0] * inv;
 }
 
 // one block of 256 threads: strided partial sums, then a fixed tree
@@ -539,33 +597,32 @@ __global__ void propose_kernel(const float* base, const float* zout, float* mo, 
     for (int c = 0; c < 3; ++c) mo[((size_t)n * 3 + c) * H * W + p] = v[c] * inv;
 }
 
-// FP32 master weights of one layer [cout][cin][3][3] + bias -> bf16 forward
-// [tap][co][ci] and data-gradient [tap'][ci][co] (tap' = 8 - tap) layouts
-__global__ void pack_kernel(const float* w, int cin, int cout, u16* wf, u16* wtr) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 9 * CH * CH) return;
-    const int tap = i / (CH * CH), co = (i / CH) % CH, ci = i % CH;
-    float v = 0.f;
-    if (co < cout && ci < cin) v = w[((co * cin + ci) * 3 + tap / 3) * 3 + tap % 3];
-    wf[i] = f2bf(v);
-    wtr[((8 - tap) * CH + ci) * CH + co] = f2bf(v);
-}
-
-// the [tap][co][ci] weight gradient back to the [cout][cin][3][3] layout
-__global__ void unpack_grad_kernel(const float* gwp, int cin, int cout, float* gw) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= cout * cin * 9) return;
-    const int tap = i % 9, ci = (i / 9) % cin, co = i / (9 * cin);
-    gw[i] = gwp[(tap * CH + co) * CH + ci];
-}
-
-__global__ void adam_kernel(float* p, const float* g, float* m1, float* m2, int n, float lr, float c1, float c2) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    m1[i] = 0.9f * m1[i] + 0.1f * gi;
-    m2[i] = 0.999f * m2[i] + 0.001f * gi * gi;
-    p[i] -= lr * (m1[i] / c1) / (sqrtf(m2[i] / c2) + 1e-8f);
+// One Adam step of every layer (lr > 0), then the FP32 master weights to
+// bf16 in the forward [tap][co][ci] and the data-gradient [tap'][ci][co]
+// (tap' = 8 - tap) layouts, zero past the layer's channels
+__global__ void update_pack_kernel(LayerSet ls, float lr, float c1, float c2) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, l = blockIdx.z;
+    if (i >= NWG + CH) return;
+    const int cin = ls.cin[l], cout = ls.cout[l];
+    auto adam = [&](float& p, float g, float& m1, float& m2) {
+        m1 = 0.9f * m1 + 0.1f * g;
+        m2 = 0.999f * m2 + 0.001f * g * g;
+        p -= lr * (m1 / c1) / (sqrtf(m2 / c2) + 1e-8f);
+    };
+    if (i < NWG) {
+        const int tap = i / (CH * CH), co = (i / CH) % CH, ci = i % CH;
+        float v = 0.f;
+        if (co < cout && ci < cin) {
+            const int o = (co * cin + ci) * 9 + tap;
+            if (lr > 0.f) adam(ls.w[l][o], ls.gw[l][o], ls.m1w[l][o], ls.m2w[l][o]);
+            v = ls.w[l][o];
+        }
+        ls.wf[l][i] = f2bf(v);
+        ls.wtr[l][((8 - tap) * CH + ci) * CH + co] = f2bf(v);
+    } else if (i - NWG < cout && lr > 0.f) {
+        const int o = i - NWG;
+        adam(ls.b[l][o], ls.gb[l][o], ls.m1b[l][o], ls.m2b[l][o]);
+    }
 }
 
 // x (float, channels-last) -> bf16
@@ -626,8 +683,7 @@ struct llg_sur {
     float* g = nullptr;                        // gradient w.r.t. a layer's output (float, 32 ch)
     u16* gz = nullptr;                         // gradient w.r.t. pre-activation (bf16)
     u16* gz2 = nullptr;                        // the same for the layer below (ping-pong)
-    float* gwp = nullptr;                      // reduced [tap][co][ci] weight gradient
-    float* part_w = nullptr;
+    float* part_w = nullptr;                   // per-block weight gradients of every layer
     float* part_b = nullptr;
     float* part2 = nullptr;                    // first-stage sums of the weight-gradient reduction
     float* part_l = nullptr;
@@ -668,11 +724,11 @@ llg_status sfail(llg_sur* s, llg_status c, const char* fmt, ...) {
                          hipGetErrorString(e_), __FILE__, __LINE__);                              \
     } while (0)
 
-// gradient rows per weight-gradient block: about WG_TARGET blocks, at
-// least 4 rows each
+// gradient rows per weight-gradient block: at least 4, and as many as let
+// one round of blocks cover the images
 int wg_rows(const llg_sur* s, int N) {
     const long long rb = (long long)((s->W + 63) / 64) * s->H * N;
-    return (int)std::min<long long>(s->H, std::max<long long>(4, (rb + WG_TARGET - 1) / WG_TARGET));
+    return (int)std::min<long long>(s->H, std::max<long long>(4, (rb + WG_ROUND - 1) / WG_ROUND));
 }
 dim3 wg_grid(const llg_sur* s, int N) {
     const int r = wg_rows(s, N);
@@ -695,27 +751,49 @@ void launch_conv(llg_sur* s, const u16* in, const u16* wt, const float* bias, fl
                        s->stream, in, wt, bias, z, zc, zb, a, zg, s->H, s->W, act, rows);
 }
 
-// weight and bias gradient of one layer from the pre-activation gradient
-// gz and the layer input ain: per-block partials, then two fixed-order
-// reduction stages into gwp ([tap][co][ci]) and gb (32 entries)
-void launch_wgrad(llg_sur* s, const u16* gz, const u16* ain, int N, float* gb) {
+// per-block weight and bias gradients of one layer from the pre-activation
+// gradient gz and the layer input ain, into slot `slot` of the partials
+void launch_wgrad(llg_sur* s, const u16* gz, const u16* ain, int N, int slot) {
     const dim3 grid = wg_grid(s, N);
-    const int nblk = (int)(grid.x * grid.y * grid.z);
-    hipLaunchKernelGGL(conv_wgrad_kernel, grid, dim3(256), 0, s->stream, gz, ain, s->part_w, s->part_b, s->H, s->W,
-                       wg_rows(s, N));
-    const int nseg = std::min(WG_SEG, nblk);
-    hipLaunchKernelGGL(wgrad_reduce1_kernel, dim3((NWG + CH + 255) / 256, nseg), dim3(256), 0, s->stream, s->part_w,
-                       s->part_b, nblk, s->part2);
-    hipLaunchKernelGGL(wgrad_reduce2_kernel, dim3((NWG + CH + 255) / 256), dim3(256), 0, s->stream, s->part2, nseg,
-                       s->gwp, gb);
+    const size_t nblk = (size_t)grid.x * grid.y * grid.z;
+    hipLaunchKernelGGL(conv_wgrad_kernel, grid, dim3(256), 0, s->stream, gz, ain, s->part_w + slot * nblk * NWG,
+                       s->part_b + slot * nblk * CH, s->H, s->W, wg_rows(s, N));
 }
 
-llg_status pack(llg_sur* s) {
+// the partials of the first `layers` slots in two fixed-order stages into
+// ls.w, ls.b
+void launch_wgrad_reduce(llg_sur* s, int N, int layers, const LayerSet& ls) {
+    const int nblk = wg_blocks(s, N), nseg = std::min(WG_SEG, nblk);
+    hipLaunchKernelGGL(wgrad_reduce1_kernel, dim3((NWG + CH + 255) / 256, nseg, layers), dim3(256), 0, s->stream,
+                       s->part_w, s->part_b, nblk, s->part2);
+    hipLaunchKernelGGL(wgrad_reduce2_kernel, dim3((NWG + CH + 255) / 256, 1, layers), dim3(256), 0, s->stream,
+                       s->part2, nseg, ls);
+}
+
+LayerSet layer_set(const llg_sur* s, float* w) {
+    LayerSet ls = {};
     for (int l = 0; l < NL; ++l) {
-        hipLaunchKernelGGL(pack_kernel, dim3((9 * CH * CH + 255) / 256), dim3(256), 0, s->stream,
-                           s->params + s->woff[l], CIN[l], COUT[l], s->wf[l], s->wtr[l]);
-        SCHK(s, hipGetLastError());
+        ls.cin[l] = CIN[l];
+        ls.cout[l] = COUT[l];
+        ls.w[l] = w + s->woff[l];
+        ls.b[l] = w + s->boff[l];
+        ls.gw[l] = s->grads + s->woff[l];
+        ls.gb[l] = s->grads + s->boff[l];
+        ls.m1w[l] = s->mom1 + s->woff[l];
+        ls.m1b[l] = s->mom1 + s->boff[l];
+        ls.m2w[l] = s->mom2 + s->woff[l];
+        ls.m2b[l] = s->mom2 + s->boff[l];
+        ls.wf[l] = s->wf[l];
+        ls.wtr[l] = s->wtr[l];
     }
+    return ls;
+}
+
+// an Adam step (lr > 0) and the bf16 weights
+llg_status update_pack(llg_sur* s, float lr, float c1, float c2) {
+    hipLaunchKernelGGL(update_pack_kernel, dim3((NWG + CH + 255) / 256, 1, NL), dim3(256), 0, s->stream,
+                       layer_set(s, s->params), lr, c1, c2);
+    SCHK(s, hipGetLastError());
     s->packed = true;
     return LLG_OK;
 }
@@ -725,9 +803,8 @@ llg_status pack(llg_sur* s) {
 // network output) is written compact, four float channels per pixel, unless
 // f32_layer asks for it; layer f32_layer's is written as float, 32 channels
 llg_status forward(llg_sur* s, const float* m, const float* B, int N, bool keep_z, int f32_layer = -1) {
-    const size_t npx = (size_t)N * s->H * s->W;
-    hipLaunchKernelGGL(make_input_kernel, dim3((unsigned)((npx + 255) / 256)), dim3(256), 0, s->stream, m, B,
-                       s->act[0], N, s->H, s->W);
+    const int hw = s->H * s->W;
+    hipLaunchKernelGGL(make_input_kernel, dim3((hw + 255) / 256, N), dim3(256), 0, s->stream, m, B, s->act[0], hw);
     SCHK(s, hipGetLastError());
     for (int l = 0; l < NL; ++l) {
         // the bias of a layer with fewer than 32 outputs is read through a
@@ -805,13 +882,12 @@ llg_status llg_sur_create(int device, int H, int W, int max_batch, llg_sur** out
     SCHK(s, hipMalloc(&s->g, npx * CH * 4));
     SCHK(s, hipMalloc(&s->gz, npx * CH * 2));
     SCHK(s, hipMalloc(&s->gz2, npx * CH * 2));
-    SCHK(s, hipMalloc(&s->gwp, 9 * CH * CH * 4));
     int maxblk = 0;
     for (int n = 1; n <= max_batch; ++n) maxblk = std::max(maxblk, wg_blocks(s, n));
-    SCHK(s, hipMalloc(&s->part_w, (size_t)maxblk * NWG * 4));
-    SCHK(s, hipMalloc(&s->part_b, (size_t)maxblk * CH * 4));
-    SCHK(s, hipMalloc(&s->part2, (size_t)WG_SEG * (NWG + CH) * 4));
-    SCHK(s, hipMalloc(&s->part_l, ((npx + 255) / 256) * 4));
+    SCHK(s, hipMalloc(&s->part_w, (size_t)NL * maxblk * NWG * 4));
+    SCHK(s, hipMalloc(&s->part_b, (size_t)NL * maxblk * CH * 4));
+    SCHK(s, hipMalloc(&s->part2, (size_t)NL * WG_SEG * (NWG + CH) * 4));
+    SCHK(s, hipMalloc(&s->part_l, ((size_t)H * W + 255) / 256 * max_batch * 4));
     SCHK(s, hipMalloc(&s->dloss, 4));
     SCHK(s, hipMalloc(&s->dm_in, npx * 3 * 4));
     SCHK(s, hipMalloc(&s->dm_t, npx * 3 * 4));
@@ -824,7 +900,7 @@ void llg_sur_destroy(llg_sur* s) {
     if (!s) return;
     (void)hipSetDevice(s->device);
     if (s->stream) (void)hipStreamSynchronize(s->stream);
-    void* ptrs[] = {s->params, s->grads, s->mom1, s->mom2, s->g, s->gz, s->gz2, s->gwp, s->part_w, s->part_b,
+    void* ptrs[] = {s->params, s->grads, s->mom1, s->mom2, s->g, s->gz, s->gz2, s->part_w, s->part_b,
                     s->part2, s->part_l, s->dloss, s->dm_in, s->dm_t, s->dm_out, s->dB};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -861,7 +937,7 @@ llg_status llg_sur_set_params(llg_sur* s, const float* params, int64_t n) {
     SCHK(s, hipMemsetAsync(s->mom1, 0, sizeof(float) * (n + CH), s->stream));
     SCHK(s, hipMemsetAsync(s->mom2, 0, sizeof(float) * (n + CH), s->stream));
     s->adam_t = 0;
-    llg_status rc = pack(s);
+    llg_status rc = update_pack(s, 0.f, 1.f, 1.f);
     if (rc != LLG_OK) return rc;
     SCHK(s, hipStreamSynchronize(s->stream));
     return LLG_OK;
@@ -916,19 +992,16 @@ llg_status llg_sur_train_step(llg_sur* s, const float* m_in, const float* m_targ
     SCHK(s, hipMemcpyAsync(s->dB, B, (size_t)batch * 3 * 4, hipMemcpyHostToDevice, s->stream));
     llg_status rc = forward(s, mi, s->dB, batch, true);
     if (rc != LLG_OK) return rc;
-    const int lb = (int)((npx + 255) / 256);
-    hipLaunchKernelGGL(loss_kernel, dim3(lb), dim3(256), 0, s->stream, s->z[NL - 1], mb, mt, s->gz, s->part_l, batch,
-                       s->H, s->W, 1.0f / s->out_scale);
+    const int hw = s->H * s->W, lb = (hw + 255) / 256 * batch;
+    hipLaunchKernelGGL(loss_kernel, dim3((hw + 255) / 256, batch), dim3(256), 0, s->stream, s->z[NL - 1], mb, mt, s->gz,
+                       s->part_l, hw, 1.0f / s->out_scale);
     SCHK(s, hipGetLastError());
     hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(256), 0, s->stream, s->part_l, lb, s->dloss);
     SCHK(s, hipGetLastError());
     u16* gcur = s->gz;    // gradient at layer l's pre-activation
     u16* gnext = s->gz2;
     for (int l = NL - 1; l >= 0; --l) {
-        launch_wgrad(s, gcur, s->act[l], batch, s->grads + s->boff[l]);
-        SCHK(s, hipGetLastError());
-        hipLaunchKernelGGL(unpack_grad_kernel, dim3((COUT[l] * CIN[l] * 9 + 255) / 256), dim3(256), 0, s->stream,
-                           s->gwp, CIN[l], COUT[l], s->grads + s->woff[l]);
+        launch_wgrad(s, gcur, s->act[l], batch, l);
         SCHK(s, hipGetLastError());
         if (l > 0) {
             // data gradient: the same convolution with flipped, transposed
@@ -940,16 +1013,12 @@ llg_status llg_sur_train_step(llg_sur* s, const float* m_in, const float* m_targ
             std::swap(gcur, gnext);
         }
     }
-    // note: the reduce kernel wrote 32 bias entries; the parameter arrays
-    // carry 32 floats of padding so this never runs past the end
+    launch_wgrad_reduce(s, batch, NL, layer_set(s, s->grads));
+    SCHK(s, hipGetLastError());
     if (lr > 0.f) {
         s->adam_t += 1;
         const float c1 = 1.0f - powf(0.9f, (float)s->adam_t), c2 = 1.0f - powf(0.999f, (float)s->adam_t);
-        const int n = (int)s->nparam;
-        hipLaunchKernelGGL(adam_kernel, dim3((n + 255) / 256), dim3(256), 0, s->stream, s->params, s->grads, s->mom1,
-                           s->mom2, n, lr, c1, c2);
-        SCHK(s, hipGetLastError());
-        rc = pack(s);
+        rc = update_pack(s, lr, c1, c2);
         if (rc != LLG_OK) return rc;
     }
     if (loss) {
@@ -1032,10 +1101,14 @@ llg_status llg_sur_conv_check(llg_sur* s, int layer, const float* x, const float
         SCHK(s, hipMemcpyAsync(s->g, gy, n * 4, hipMemcpyHostToDevice, s->stream));
         hipLaunchKernelGGL(act_bwd_kernel, dim3(nb), dim3(256), 0, s->stream, s->g, (const float*)nullptr, s->gz, n, 0);
         SCHK(s, hipGetLastError());
-        launch_wgrad(s, s->gz, s->act[0], batch, dgb);
+        launch_wgrad(s, s->gz, s->act[0], batch, 0);
         SCHK(s, hipGetLastError());
-        hipLaunchKernelGGL(unpack_grad_kernel, dim3((COUT[layer] * CIN[layer] * 9 + 255) / 256), dim3(256), 0,
-                           s->stream, s->gwp, CIN[layer], COUT[layer], dgw);
+        LayerSet ls = {};
+        ls.cin[0] = CIN[layer];
+        ls.cout[0] = COUT[layer];
+        ls.w[0] = dgw;
+        ls.b[0] = dgb;
+        launch_wgrad_reduce(s, batch, 1, ls);
         SCHK(s, hipGetLastError());
         launch_conv(s, s->gz, s->wtr[layer], nullptr, s->z[1], nullptr, nullptr, nullptr, nullptr, batch, 0);
         SCHK(s, hipGetLastError());
@@ -1180,15 +1253,19 @@ llg_status llg_sur_advance(llg_sur* s, const llg_film_desc* film, int window, in
                 if ((rc = verify(launched++)) != LLG_OK) return rc;
             const float* prev = P + (size_t)(j - 1) * stride;
             const float* base = prev;
+            // (the coarse step on its batch's stream, the network beside it)
             if (predictor != LLG_SUR_BASE_STATE) {
                 float* em = nullptr;
                 rc = llg_batch_fixed_async_(s->eb, coarse, dt * seg_steps, 1, prev, 0, 1, s->stream, &em);
-                if (rc == LLG_OK) rc = llg_batch_then_(s->eb, s->stream);
                 if (rc != LLG_OK) return sfail(s, rc, "predictor batch: %s", llg_batch_last_error(s->eb));
                 base = em;
             }
             rc = forward(s, prev, s->dB, 1, false);
             if (rc != LLG_OK) return rc;
+            if (predictor != LLG_SUR_BASE_STATE) {
+                rc = llg_batch_then_(s->eb, s->stream);
+                if (rc != LLG_OK) return sfail(s, rc, "predictor batch: %s", llg_batch_last_error(s->eb));
+            }
             hipLaunchKernelGGL(propose_kernel, dim3((ncells + 255) / 256), dim3(256), 0, s->stream, base,
                                s->z[NL - 1], P + (size_t)j * stride, 1, s->H, s->W, s->out_scale);
             SCHK(s, hipGetLastError());
