@@ -1305,21 +1305,29 @@ __global__ __launch_bounds__((ColSplit<L, E, NQ>::NT)) void col2d_fast(Col2dArgs
 #define FAST2D_PART 0
 #endif
 constexpr int kParts = 5;
+// Variant 0, the default, is the faster one on the length's square film (us
+// per Dormand-Prince attempt, variant 0 and 1, rows and columns together):
+// 96 x 96 117 and 183 (few elements per lane mean more blocks, and these films
+// do not fill the chip: six against twelve), 192 x 192 126 and 181, 384 x 384
+// 167 and 206, 512 x 512 185 (four classes of rows) and 191, 1024 x 1024
+// columns 561 and 581.  A batch that fills the chip prefers twelve elements
+// in the 384-point rows (170 against 177 us per evaluation of 64 films), but
+// a film takes the same variant alone and in a batch.
 // rows: (Px, elements per lane, frequency classes, variant)
 #define ROW_VARIANTS_0(X)
-#define ROW_VARIANTS_1(X) X(64, 4, 2, 0) X(64, 8, 2, 1) X(128, 4, 2, 0) X(128, 4, 4, 1) X(192, 12, 2, 0)  \
-    X(192, 6, 2, 1) X(256, 4, 2, 0) X(256, 4, 4, 1)
-#define ROW_VARIANTS_2(X) X(384, 12, 2, 0) X(384, 6, 4, 1) X(512, 4, 2, 0) X(512, 4, 4, 1) X(768, 12, 2, 0) \
-    X(768, 6, 4, 1)
-#define ROW_VARIANTS_3(X) X(1024, 8, 2, 0) X(1024, 4, 4, 1) X(1536, 12, 4, 0) X(1536, 12, 2, 1)
+#define ROW_VARIANTS_1(X) X(64, 4, 2, 0) X(64, 8, 2, 1) X(128, 4, 2, 0) X(128, 4, 4, 1) X(192, 6, 2, 0)   \
+    X(192, 12, 2, 1) X(256, 4, 2, 0) X(256, 4, 4, 1)
+#define ROW_VARIANTS_2(X) X(384, 6, 2, 0) X(384, 12, 2, 1) X(512, 4, 2, 0) X(512, 4, 4, 1) X(768, 6, 2, 0)  \
+    X(768, 12, 2, 1)
+#define ROW_VARIANTS_3(X) X(1024, 4, 4, 0) X(1024, 8, 2, 1) X(1536, 12, 4, 0) X(1536, 12, 2, 1)
 #define ROW_VARIANTS_4(X) X(2048, 8, 4, 0) X(2048, 16, 2, 1) X(4096, 16, 4, 0) X(4096, 32, 2, 1)
 // columns: (L = Py/2, elements per lane, frequency classes, variant)
-#define COL_VARIANTS_0(X) X(32, 4, 2, 0) X(32, 8, 2, 1) X(64, 4, 2, 0) X(64, 4, 4, 1) X(96, 12, 2, 0)      \
-    X(96, 6, 2, 1) X(128, 4, 2, 0) X(128, 4, 4, 1) X(192, 12, 2, 0) X(192, 6, 4, 1) X(256, 4, 2, 0)        \
+#define COL_VARIANTS_0(X) X(32, 4, 2, 0) X(32, 8, 2, 1) X(64, 4, 2, 0) X(64, 4, 4, 1) X(96, 6, 2, 0)       \
+    X(96, 12, 2, 1) X(128, 4, 2, 0) X(128, 4, 4, 1) X(192, 6, 2, 0) X(192, 12, 2, 1) X(256, 4, 2, 0)        \
     X(256, 4, 4, 1)
-#define COL_VARIANTS_1(X) X(384, 12, 2, 0) X(384, 6, 4, 1)
+#define COL_VARIANTS_1(X) X(384, 6, 2, 0) X(384, 12, 2, 1)
 #define COL_VARIANTS_2(X) X(512, 8, 2, 0) X(512, 4, 4, 1)
-#define COL_VARIANTS_3(X) X(768, 12, 2, 0) X(768, 6, 4, 1) X(1024, 16, 2, 0) X(1024, 8, 4, 1)
+#define COL_VARIANTS_3(X) X(768, 12, 2, 0) X(768, 6, 4, 1) X(1024, 8, 4, 0) X(1024, 16, 2, 1)
 #define COL_VARIANTS_4(X) X(2048, 16, 4, 0) X(2048, 32, 2, 1)
 #define ROW_VARIANTS(X) ROW_VARIANTS_0(X) ROW_VARIANTS_1(X) ROW_VARIANTS_2(X) ROW_VARIANTS_3(X) ROW_VARIANTS_4(X)
 #define COL_VARIANTS(X) COL_VARIANTS_0(X) COL_VARIANTS_1(X) COL_VARIANTS_2(X) COL_VARIANTS_3(X) COL_VARIANTS_4(X)

@@ -88,15 +88,18 @@ template <typename C> struct Dft<6, C> {
 
 // ---------------------------------------------------------------------------
 // stage plan: greedy radices from {16, 8, 4, 2, 3, 5, 7}, each dividing both
-// the remaining length and E.  With 12 (6) elements per lane the factor 3
-// is taken together with the last 4 (2) as one radix-12 (radix-6) stage, one
-// LDS exchange less than a radix-3 stage of its own (64 films of 64 ... 256
-// cells, RK4: 24.22 -> 23.70 ms per 30 steps); it comes last, so that every
-// earlier stage's sub-length stays a power of two.
+// the remaining length and E.
+//
+// With 12 (6) elements per lane, lengths 3 * 2^k: the first stage has radix 4
+// (2) and the last, which holds the factor 3, radix 12 (6), because they work
+// on the lane's own elements; what lies between passes through LDS only, so
+// its radices need not divide E and are chosen large with three quarters of
+// the lanes busy: 96 = 2 x 8 x 6, 192 = 2 x 4 x 4 x 6, 384 = 2 x 8 x 4 x 6
+// with six elements, 384 = 4 x 8 x 12, 768 = 4 x 16 x 12 with twelve; all
+// sub-lengths before the last stage are powers of two.
 // ---------------------------------------------------------------------------
+constexpr bool lf_three(int L, int E) { return (E == 12 || E == 6) && L % (2 * E) == 0; }
 constexpr int lf_pick(int rem, int E) {
-    if (E == 12 && rem % 12 == 0) return rem == 12 ? 12 : (rem / 12) % 4 == 0 ? 4 : (rem / 12) % 2 == 0 ? 2 : 3;
-    if (E == 6 && rem % 6 == 0) return rem == 6 ? 6 : (rem / 6) % 2 == 0 ? 2 : 3;
     return (rem % 16 == 0 && E % 16 == 0) ? 16
          : (rem % 8 == 0 && E % 8 == 0) ? 8
          : (rem % 4 == 0 && E % 4 == 0) ? 4
@@ -105,7 +108,21 @@ constexpr int lf_pick(int rem, int E) {
          : (rem % 5 == 0 && E % 5 == 0) ? 5
          : (rem % 7 == 0 && E % 7 == 0) ? 7 : 0;
 }
+constexpr int lf_three_radix(int L, int E, int s) {
+    const int first = E == 12 && L % 48 == 0 ? 4 : 2;
+    int mid = L / (first * E);
+    if (s == 0) return first;
+    for (int i = 1; mid > 1; ++i) {
+        const int r = mid == 16 ? (E == 12 ? 16 : 4) : mid % 8 == 0 ? 8 : mid % 4 == 0 ? 4 : 2;
+        if (i == s) return r;
+        mid /= r;
+        if (mid == 1 && i + 1 == s) return E;
+        if (mid == 1) return 1;
+    }
+    return s == 1 ? E : 1;
+}
 constexpr int lf_radix(int L, int E, int s) {
+    if (lf_three(L, E)) return lf_three_radix(L, E, s);
     int rem = L;
     for (int i = 0; i < s; ++i) {
         const int r = lf_pick(rem, E);
@@ -117,8 +134,8 @@ constexpr int lf_radix(int L, int E, int s) {
 constexpr int lf_nstages(int L, int E) {
     int rem = L, n = 0;
     while (rem > 1) {
-        const int r = lf_pick(rem, E);
-        if (r == 0) return -1;
+        const int r = lf_radix(L, E, n);
+        if (r <= 1 || rem % r != 0) return -1;
         rem /= r;
         ++n;
     }
@@ -218,10 +235,12 @@ struct LaneFFT {
     static __device__ __forceinline__ void stage(C (&x)[E], C* sc, const C* tws, int lg) {
         constexpr int R = lf_radix(L, E, S);
         constexpr int Ns = lf_ns(L, E, S);
-        constexpr int U = E / R;          // butterflies per lane
-        constexpr int LR = L / R;
+        constexpr int LR = L / R;         // butterflies
+        constexpr int U = (LR + P - 1) / P;   // per lane
+        constexpr bool FULL = LR % P == 0;    // every lane has U of them
         constexpr int B = tws_off(S);
         constexpr bool FIRST = S == 0, LAST = S == NS - 1;
+        static_assert((!FIRST && !LAST) || E == U * R, "the first and the last stage work on the lane's elements");
         // power-of-two lengths: every radix, Ns and P are powers of two, so a
         // scratch index splits into the lane's part and a part fixed by
         // (u, r) with disjoint bits, and the swizzle (linear over XOR) of the
@@ -233,6 +252,7 @@ struct LaneFFT {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int j = lg + P * u;
+            if (!FULL && j >= LR) continue;
 #pragma unroll
             for (int r = 0; r < R; ++r)
                 v[u][r] = FIRST ? x[u + r * U]
@@ -260,6 +280,7 @@ struct LaneFFT {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int j = lg + P * u;
+                if (!FULL && j >= LR) continue;
                 const int k = cmod<Ns>(j);
                 const int d = (j - k) * R + k;
 #pragma unroll
