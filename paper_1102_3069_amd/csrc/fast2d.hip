@@ -159,7 +159,7 @@ struct RowSplit {
     // wavefront share kind and class
     static __device__ __forceinline__ void group(int gi, int& kind, int& q, int& pair) {
         pair = gi % RP;
-        const int kq = gi / RP;
+        const int kq = __builtin_amdgcn_readfirstlane(gi / RP);   // 64 / P = RP groups a wavefront
         q = kq % NQ;
         kind = kq / NQ;
     }
@@ -211,10 +211,16 @@ struct RowSplit {
             __syncthreads();
             pz = scr + group_of(kind, (NQ - q) % NQ, pair) * SC;
         }
-        const int cs = g.nrows * g.nkxp;
+        const size_t cs = (size_t)g.nrows * g.nkxp;
         const float2 zN = z[E2 / 2];   // X[PX/2]: class 0, lane 0
-        float2* s0 = NAT ? S + r0 * g.nkxp : S + (r0 << g.tsh);
-        float2* s1 = NAT ? s0 + g.nkxp : s0 + (1 << g.tsh);
+        // what the group's transform holds: the x and y components of one
+        // row (A, B), or the z components of both rows
+        const int rowstep = NAT ? g.nkxp : 1 << g.tsh;
+        float2* sA = S + (size_t)rb * rowstep + (kind == 2 ? 2 * cs : 0);
+        float2* sB = kind == 2 ? sA : sA + cs;
+        const uint32_t oA = (uint32_t)((2 * pair + (kind == 1 ? 1 : 0)) * rowstep);
+        const uint32_t oB = kind == 2 ? oA + (uint32_t)rowstep : oA;
+        const bool wA = kind == 1 ? v1 : v0, wB = kind == 0 ? v0 : v1;
 #pragma unroll
         for (int i = 0; i < E2 / 2; ++i) {
             const int j = lg + P * i;
@@ -229,27 +235,14 @@ struct RowSplit {
                 A = mk2(zk.x, zN.x);
                 B = mk2(zk.y, zN.y);
             }
-            const int col = NAT ? NQ * j + q : tile_index(0, q * QC + j, g.nrows, g.tsh);
-            if (kind == 0) {
-                if (v0) { s0[col] = A; s0[cs + col] = B; }
-            } else if (kind == 1) {
-                if (v1) { s1[col] = A; s1[cs + col] = B; }
-            } else {
-                if (v0) s0[2 * cs + col] = A;
-                if (v1) s1[2 * cs + col] = B;
-            }
+            const uint32_t col = NAT ? NQ * j + q : tile_index(0, q * QC + j, g.nrows, g.tsh);
+            if (wA) elem32(sA, oA + col) = A;
+            if (wB) elem32(sB, oB + col) = B;
         }
         if (NAT && q == 0 && lg == 0) {   // the real Nyquist coefficients, column PX/2
             const float2 A = mk2(zN.x, 0.f), B = mk2(zN.y, 0.f);
-            const int col = PX / 2;
-            if (kind == 0) {
-                if (v0) { s0[col] = A; s0[cs + col] = B; }
-            } else if (kind == 1) {
-                if (v1) { s1[col] = A; s1[cs + col] = B; }
-            } else {
-                if (v0) s0[2 * cs + col] = A;
-                if (v1) s1[2 * cs + col] = B;
-            }
+            if (wA) elem32(sA, oA + PX / 2) = A;
+            if (wB) elem32(sB, oB + PX / 2) = B;
         }
     }
 };
@@ -431,15 +424,18 @@ __device__ __forceinline__ void local_field_lds(const Grid& g, const Phys& p, co
 __device__ __forceinline__ unsigned z_neighbours(const Grid& g, const Phys& p, const float* __restrict__ m, int r,
                                                  int z, int x, float (&lo)[3], float (&up)[3]) {
     if (p.cex[2] == 0.f || g.nz < 2) return 0u;
-    const long long cs = g.ncells;
-    const long long i = (long long)r * g.nx + x, sl = (long long)g.ny * g.nx;
-    long long il = -1, iu = -1;
-    if (z > 0) il = i - sl; else if (g.pbc[2]) il = i + (long long)(g.nz - 1) * sl;
-    if (z < g.nz - 1) iu = i + sl; else if (g.pbc[2]) iu = i - (long long)(g.nz - 1) * sl;
-    unsigned mask = 0u;
-    if (il >= 0) { lo[0] = m[il]; lo[1] = m[cs + il]; lo[2] = m[2 * cs + il]; mask |= 1u; }
-    if (iu >= 0) { up[0] = m[iu]; up[1] = m[cs + iu]; up[2] = m[2 * cs + iu]; mask |= 2u; }
-    return mask;
+    const uint32_t cs = (uint32_t)g.ncells, sl = (uint32_t)g.ny * (uint32_t)g.nx;
+    const uint32_t i = (uint32_t)r * (uint32_t)g.nx + (uint32_t)x;
+    const bool hl = z > 0 || g.pbc[2], hu = z < g.nz - 1 || g.pbc[2];
+    const uint32_t il = z > 0 ? i - sl : i + (uint32_t)(g.nz - 1) * sl;
+    const uint32_t iu = z < g.nz - 1 ? i + sl : i - (uint32_t)(g.nz - 1) * sl;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const float* mc = m + (size_t)c * cs;
+        if (hl) lo[c] = elem32(mc, il);
+        if (hu) up[c] = elem32(mc, iu);
+    }
+    return (hl ? 1u : 0u) | (hu ? 2u : 0u);
 }
 
 // exchange terms of a 3D grid that the staged rows of a block do not hold:
@@ -449,13 +445,13 @@ __device__ __forceinline__ void exchange_wrap_z(const Grid& g, const Phys& p, co
                                                 int x, int y, float mx, float my, float mz, const float (&lo)[3],
                                                 const float (&up)[3], unsigned zmask, float& hx, float& hy,
                                                 float& hz) {
-    const long long cs = g.ncells;
+    const size_t cs = g.ncells;
     float sx = 0.f, sy = 0.f, sz = 0.f;
     auto nb = [&](int rr, float c) {
-        const long long i = (long long)rr * g.nx + x;
-        sx += c * (m[i] - mx);
-        sy += c * (m[cs + i] - my);
-        sz += c * (m[2 * cs + i] - mz);
+        const uint32_t i = (uint32_t)rr * (uint32_t)g.nx + (uint32_t)x;
+        sx += c * (elem32(m, i) - mx);
+        sy += c * (elem32(m + cs, i) - my);
+        sz += c * (elem32(m + 2 * cs, i) - mz);
     };
     if (p.cex[1] != 0.f && g.ny > 1 && g.pbc[1]) {
         if (y == 0) nb(r + g.ny - 1, p.cex[1]);
@@ -467,7 +463,16 @@ __device__ __forceinline__ void exchange_wrap_z(const Grid& g, const Phys& p, co
     hx += sx; hy += sy; hz += sz;
 }
 
-// XPER: the x axis is periodic (nx == PX), else nx <= PX/2
+// XPER: the x axis is periodic (nx == PX), else nx <= PX/2.
+// Bound by latency and vector instructions, not by memory: of the 2658 vector
+// instructions of a 512-point row some 750 are the transforms and the torque,
+// most others addresses.  Bases that a wavefront shares (a component of the
+// block's rows) stay in scalar registers with 32-bit offsets per lane, and
+// kind, class and the weights that are not zero are known to be uniform
+// (2536 instructions): 256x256x64 thermal Heun 4633 -> 4528 us per 10 steps,
+// 2048x2048 Dormand-Prince 26.94 -> 26.47 ms per 2 ps, 64-film RK4
+// 21.80 -> 21.57 ms per 30 steps; a 512x512 film, whose 256 blocks run one per
+// compute unit, is unchanged
 template <int PX, int E2, int NQ, bool XPER, bool NAT>
 __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const float2* __restrict__ twx,
                                              float2* __restrict__ S, const StageArgs& sa,
@@ -506,7 +511,8 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
     auto plane_of = [&](int ri, int& y, int& z) {
         y = y0 + ri;
         z = z0;
-        while (y >= ny) { y -= ny; ++z; }
+        if constexpr (NAT)
+            while (y >= ny) { y -= ny; ++z; }
     };
     const int cs = g.ncells;
     const bool stage = sa.mode == ROW_STAGE;
@@ -527,19 +533,13 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
     // (NQ - q) mod NQ, index LQ - j for q = 0, LQ - 1 - j otherwise): the
     // loads (in the first round unless E2 > 8), then the conjugations and
     // the packed DC / Nyquist column
-    const int scs = g.nrows * g.nkxp;
-    const float2* sa_ = nullptr;
-    const float2* sb_ = nullptr;
-    if (p.demag_on) {
-        const int rs0 = NAT ? r0 * g.nkxp : (r0 << g.tsh);
-        const int rs1 = NAT ? (r0 + 1) * g.nkxp : ((r0 + 1) << g.tsh);
-        if (kind == 0) { if (v0) { sa_ = S + rs0; sb_ = sa_ + scs; } }
-        else if (kind == 1) { if (v1) { sa_ = S + rs1; sb_ = sa_ + scs; } }
-        else {
-            if (v0) sa_ = S + 2 * scs + rs0;
-            if (v1) sb_ = S + 2 * scs + rs1;
-        }
-    }
+    const size_t scs = (size_t)g.nrows * g.nkxp;
+    const int rowstep = NAT ? g.nkxp : 1 << g.tsh;
+    const float2* sA = S + (size_t)rb * rowstep + (kind == 2 ? 2 * scs : 0);
+    const float2* sB = kind == 2 ? sA : sA + scs;
+    const uint32_t oA = (uint32_t)((2 * pair + (kind == 1 ? 1 : 0)) * rowstep);
+    const uint32_t oB = kind == 2 ? oA + (uint32_t)rowstep : oA;
+    const bool rA = kind == 1 ? v1 : v0, rB = kind == 0 ? v0 : v1;
     auto spec_col = [&](int i) {
         const int j = lg + P * i;
         const int k = NQ * j + q;
@@ -567,9 +567,9 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
     auto spec_load = [&](int i0) {
 #pragma unroll
         for (int ii = 0; ii < CZ; ++ii) {
-            const int col = spec_col(i0 + ii);
-            za[ii] = sa_ ? sa_[col] : mk2(0.f, 0.f);
-            zb[ii] = sb_ ? sb_[col] : mk2(0.f, 0.f);
+            const uint32_t col = spec_col(i0 + ii);
+            za[ii] = rA ? elem32(sA, oA + col) : mk2(0.f, 0.f);
+            zb[ii] = rB ? elem32(sB, oB + col) : mk2(0.f, 0.f);
         }
     };
     if (p.demag_on) spec_load(0);
@@ -607,7 +607,8 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
     };
     auto row_src = [&](int rc, bool& ok) {
         const int rq = rc / 3, c = rc - 3 * rq;
-        return mi + (size_t)c * cs + (size_t)staged_row(rq, ok) * nx;
+        const int row = staged_row(rq, ok);
+        return mi + ((uint32_t)c * (uint32_t)cs + (uint32_t)row * (uint32_t)nx);   // (3 ncells < 2^32)
     };
     constexpr int CR = ROW1 ? ITR : 8;           // 16-byte units per round
     float rv[4 * CR];
@@ -661,9 +662,11 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
     float mnx[MAXIT], mny[MAXIT], mnz[MAXIT];   // the new stage state, held until the staged rows are free
     constexpr int KP = kMaxK - 1;
     const int nprev = (stage || errm) ? sa.nk - 1 : 0;
-    auto used = [&](int j) {
-        return j < nprev && ((stage && dtau * sa.a[j] != 0.f) || (errm && sa.e[j] != 0.f));
-    };
+    // (as bits: the weights sit in scalar registers)
+    auto nonzero = [](float w) { return (__float_as_uint(w) << 1) != 0u; };
+    auto used_a = [&](int j) { return stage && nonzero(sa.a[j]); };
+    auto used_e = [&](int j) { return errm && nonzero(sa.e[j]); };
+    auto used = [&](int j) { return j < nprev && (used_a(j) || used_e(j)); };
     constexpr bool KSER = MAXIT > 8;
     // values in flight per round: fewer in 3D, whose blocks share a compute
     // unit three at a time (and whose integrators combine few stages)
@@ -671,7 +674,11 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
     constexpr int ITC = KSER ? 1 : (MAXIT * 3 <= KBUD ? MAXIT : KBUD / 3);
     constexpr int KB0 = KBUD / (3 * ITC);
     constexpr int KB = KB0 < 1 ? 1 : (KB0 > KP ? KP : KB0);
-    int qq_[KSER ? 1 : MAXIT];   // this thread's cells (-1: none)
+    // this thread's cells, for the loads (past the end of the block's: its
+    // last one, so that only whole wavefronts are skipped, by a scalar branch)
+    uint32_t qq_[KSER ? 1 : MAXIT];
+    const int wave0 = __builtin_amdgcn_readfirstlane(tid);
+    auto idle = [&](int it) { return wave0 + it * NT >= ncb; };
     auto k_load = [&](int i0, int j0, float (&kv)[KB][ITC][3]) {
 #pragma unroll
         for (int jj = 0; jj < KB && j0 + jj < KP; ++jj) {
@@ -680,9 +687,10 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
             const float* __restrict__ kj = resolve(sa.kprev[j], cur);
 #pragma unroll
             for (int ii = 0; ii < ITC && i0 + ii < MAXIT; ++ii) {
-                const int qq = qq_[KSER ? 0 : i0 + ii];
-                if (qq < 0) continue;
-                kv[jj][ii][0] = kj[qq]; kv[jj][ii][1] = kj[cs + qq]; kv[jj][ii][2] = kj[2 * cs + qq];
+                if (idle(i0 + ii)) continue;
+                const uint32_t qq = qq_[KSER ? 0 : i0 + ii];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) kv[jj][ii][c] = elem32(kj + (size_t)c * cs, qq);
             }
         }
     };
@@ -696,10 +704,10 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
 #pragma unroll
             for (int ii = 0; ii < ITC && i0 + ii < MAXIT; ++ii) {
                 const int it = i0 + ii;
-                if (qq_[KSER ? 0 : it] < 0) continue;
+                if (idle(it)) continue;
                 const float vx = kv[jj][ii][0], vy = kv[jj][ii][1], vz = kv[jj][ii][2];
-                if (ca != 0.f) { px_[it] += ca * vx; py_[it] += ca * vy; pz_[it] += ca * vz; }
-                if (ce != 0.f) { ex_[it] += ce * vx; ey_[it] += ce * vy; ez_[it] += ce * vz; }
+                if (used_a(j)) { px_[it] += ca * vx; py_[it] += ca * vy; pz_[it] += ca * vz; }
+                if (used_e(j)) { ex_[it] += ce * vx; ey_[it] += ce * vy; ez_[it] += ce * vz; }
             }
         }
     };
@@ -711,14 +719,14 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
 #pragma unroll
         for (int it = 0; it < MAXIT; ++it) {
             px_[it] = py_[it] = pz_[it] = ex_[it] = ey_[it] = ez_[it] = 0.f;
-            qq_[it] = -1;
-            const int e = tid + it * NT;
-            if (e >= ncb || !(stage || errm)) continue;
-            int ri, x;
-            split_cell(e, nx, rnx, ri, x);
-            const int qq = (rb + ri) * nx + x;
+            // (a block's cells are consecutive)
+            const uint32_t qq = (uint32_t)rb * (uint32_t)nx + (uint32_t)min(tid + it * NT, ncb - 1);
             qq_[it] = qq;
-            if (stage) { px_[it] = m0[qq]; py_[it] = m0[cs + qq]; pz_[it] = m0[2 * cs + qq]; }
+            if (stage && !idle(it)) {
+                px_[it] = elem32(m0, qq);
+                py_[it] = elem32(m0 + cs, qq);
+                pz_[it] = elem32(m0 + 2 * (size_t)cs, qq);
+            }
         }
     };
     if constexpr (KSER) {
@@ -873,10 +881,10 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
         } else {
             local_field_lds(g, p, rm, rc, rp, cstr, r, x, step, hx, hy, hz);
         }
-        const int qq = r * nx + x;
+        const uint32_t qq = (uint32_t)r * (uint32_t)nx + (uint32_t)x;
         if (sa.mode == ROW_EVAL) {
             float* h = global_ptr(sa.h_out);
-            h[qq] = hx * p.Ms; h[cs + qq] = hy * p.Ms; h[2 * cs + qq] = hz * p.Ms;
+            elem32(h, qq) = hx * p.Ms; elem32(h + cs, qq) = hy * p.Ms; elem32(h + 2 * (size_t)cs, qq) = hz * p.Ms;
             bad |= !(isfinite(hx) && isfinite(hy) && isfinite(hz));
             continue;
         }
@@ -907,7 +915,7 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
             stt_torque(p, mx, my, mz, Dx, Dy, Dz, kx, ky, kz);
         }
         bad |= !(isfinite(kx) && isfinite(ky) && isfinite(kz));
-        if (ko) { ko[qq] = kx; ko[cs + qq] = ky; ko[2 * cs + qq] = kz; }
+        if (ko) { elem32(ko, qq) = kx; elem32(ko + cs, qq) = ky; elem32(ko + 2 * (size_t)cs, qq) = kz; }
         if (sa.mode == ROW_KONLY) {
             if (errm) errmax = fmaxf(errmax, sqrtf(kx * kx + ky * ky + kz * kz));
             continue;
@@ -925,7 +933,7 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
         if (stage) {
             const float inv = rsqrtf(ax * ax + ay * ay + az * az);
             ax *= inv; ay *= inv; az *= inv;
-            mo[qq] = ax; mo[cs + qq] = ay; mo[2 * cs + qq] = az;
+            elem32(mo, qq) = ax; elem32(mo + cs, qq) = ay; elem32(mo + 2 * (size_t)cs, qq) = az;
             mnx[it] = ax; mny[it] = ay; mnz[it] = az;
         }
         if (errm) errmax = fmaxf(errmax, dtau * sqrtf(ex * ex + ey * ey + ez * ez));

@@ -111,6 +111,19 @@ __device__ __forceinline__ T* global_ptr(T* const& p) {
     return (T*)*(const gptr*)&p;
 }
 
+// Element i of an array with a base that is the same for the whole wavefront:
+// the byte offset stays in 32 bits (arrays below 4 GiB: one component of a
+// field), so the access takes the base from scalar registers and needs no
+// 64-bit address arithmetic per lane.
+template <typename T>
+__device__ __forceinline__ T& elem32(T* base, uint32_t i) {
+    return *(T*)((char*)base + (uint32_t)(i * (uint32_t)sizeof(T)));
+}
+template <typename T>
+__device__ __forceinline__ const T& elem32(const T* base, uint32_t i) {
+    return *(const T*)((const char*)base + (uint32_t)(i * (uint32_t)sizeof(T)));
+}
+
 // A buffer argument that may follow the state-buffer swap:
 // sel 0 -> p[0]; sel 1 -> p[cur]; sel 2 -> p[cur ^ 1].
 struct BufRef {

@@ -1357,6 +1357,13 @@ llg_status llg_profile_evals(llg_solver* s, int n, double* ms_out, int n_kinds, 
             }
         } guard{ev};
         hipEvent_t* T = &ev[2 * (size_t)np * n];
+        // the wall time of an evaluation from `n` launched plainly back to
+        // back; the launches that carry events follow behind them, so that
+        // none of those starts on an idle device
+        HIPCHK(s, hipEventRecord(T[0], s->stream));
+        for (int i = 0; i < n; ++i)
+            if ((rc = eval_into(s, s->hbuf, p)) != LLG_OK) return rc;
+        HIPCHK(s, hipEventRecord(T[1], s->stream));
         for (int i = 0; i < n; ++i) {
             g_kernel_timing = KernelTiming{&ev[2 * (size_t)np * i], np};
             if ((rc = launch_fwd_plain(s, 1)) != LLG_OK) return rc;
@@ -1372,12 +1379,6 @@ llg_status llg_profile_evals(llg_solver* s, int n, double* ms_out, int n_kinds, 
             if (g_kernel_timing.left != 0) return fail(s, LLG_E_DEVICE, "an evaluation launched fewer kernels than timed");
         }
         g_kernel_timing = KernelTiming{};
-        // the wall time of an evaluation from `n` more, launched plainly
-        // back to back (the timed launches above carry their events)
-        HIPCHK(s, hipEventRecord(T[0], s->stream));
-        for (int i = 0; i < n; ++i)
-            if ((rc = eval_into(s, s->hbuf, p)) != LLG_OK) return rc;
-        HIPCHK(s, hipEventRecord(T[1], s->stream));
         if ((rc = sync(s)) != LLG_OK) return rc;
         // pair index -> kernel kind (0 fwd, 1 spectral / z, 2 inv, 3 y fwd, 4 y inv)
         const int kind2[3] = {0, 1, 2}, kind3[5] = {0, 3, 1, 4, 2};
