@@ -113,7 +113,9 @@ const char *llg_last_error(const llg_solver *s);
  * `pbc_images` (>= 0) periodic images are added per periodic axis on each
  * side.  Open axes are zero padded to an FFT length >= 2n made of the
  * factors 2, 3, 5, 7 (Sec. 3.3): the shortest one, or the next one with
- * compiled kernels.  Invalidates m and the demag kernel.
+ * compiled kernels; periodic axes keep their length, or are padded likewise
+ * (the kernel continued periodically) where it has no compiled kernels.
+ * Invalidates m and the demag kernel.
  * LLG_E_UNSUPPORTED if a padded length exceeds the library's limits
  * (x: 2048, y and z: 4096; x up to 4096 for one-cell-thick films whose
  * padded y length has a compiled column kernel, e.g. 2048 x 2048).
@@ -174,7 +176,9 @@ llg_status llg_eval_heff(llg_solver *s, float *h_out, llg_mem where);
  * they are.  The spectrum and a private copy of the device state live in a
  * static device array of 32 MiB per GPU (held until the process ends), so no
  * call allocates or frees anything: films up to 1024 x 1024 cells in 2D;
- * LLG_E_UNSUPPORTED where a geometry's spectra would not fit.  LLG_E_STATE
+ * LLG_E_UNSUPPORTED where a geometry's spectra, at the shortest FFT lengths,
+ * would not fit (where only the padding to compiled lengths outgrows the
+ * array, llg_set_geometry allocated the room).  LLG_E_STATE
  * until the demag kernel spectrum exists (its build allocates: call
  * llg_eval_heff, llg_step or llg_run once first).  Every call on one GPU
  * shares that array: calls that overlap on one GPU (several solvers on

@@ -38,7 +38,8 @@ inline void hot_launch(F kernel, const dim3& grid, const dim3& block, uint32_t s
 
 // Geometry of the cell grid and of the convolution (FFT) grid.
 //   rows  = ny*nz x-rows of nx cells, row r = k*ny + j
-//   P*    = FFT length per axis (2n or more on open axes, n on periodic ones)
+//   P*    = FFT length per axis (2n or more on open axes; periodic ones n, or 2n or
+//           more where n itself has no compiled kernels)
 //   nkx   = Px/2 + 1 retained x frequencies (real-to-complex)
 //   nkxp  = row stride of the spectrum buffers (nkx rounded up to 16)
 struct Grid {
@@ -47,7 +48,7 @@ struct Grid {
     int pbc[3];
     int Px, Py, Pz;
     int nkx, nkxp;
-    int split_y, split_z;   // 1 on an open axis: even/odd half transforms
+    int split_y, split_z;   // 1 on an axis padded to twice its cells or more: even/odd half transforms
     int tsh;                // 2D compiled path: spectrum columns in tiles of 2^tsh
     int rvar, cvar;         // compiled-length kernels: variant of the row length Px and of
                             // the column half length Py/2, fixed when the solver or batch

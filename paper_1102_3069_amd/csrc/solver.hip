@@ -137,6 +137,8 @@ struct llg_solver {
     double K_resid = 0.0;
     float2* S = nullptr;
     float2* Sy = nullptr;
+    char* noalloc = nullptr;  // scratch of llg_eval_heff_noalloc where only the padding to
+                              // compiled lengths outgrows the static array
     float* mbuf[2] = {nullptr, nullptr};
     float* ms[2] = {nullptr, nullptr};
     float* kb[6] = {};
@@ -192,6 +194,7 @@ void free_buffers(llg_solver* s) {
     free_dev(s->K); s->K = nullptr;
     free_dev(s->S); s->S = nullptr;
     free_dev(s->Sy); s->Sy = nullptr;
+    free_dev(s->noalloc); s->noalloc = nullptr;
     for (auto& p : s->mbuf) { free_dev(p); p = nullptr; }
     for (auto& p : s->ms) { free_dev(p); p = nullptr; }
     for (auto& p : s->kb) { free_dev(p); p = nullptr; }
@@ -226,38 +229,52 @@ size_t noalloc_need(const int n[3], const int P[3]) {
     return kNoAllocStateBytes + (row * (size_t)n[1] * n[2] + 255) / 256 * 256 + sy;
 }
 
-// Lengthens the open axes' FFT lengths P (the shortest 2-3-5-7 lengths >=
-// 2n) to the next lengths with compiled kernels where every pass then runs
-// compiled: zero padding beyond 2n - 1 leaves the convolution unchanged
-// (Sec. 3.2).  RK4 at 250 x 63 cells: 61 us per evaluation with the
-// runtime-length kernels at 500 x 126 points, 18 with the compiled ones at
-// 512 x 128; at 1000 x 600 cells 322 (2000 x 1200 points) against 87 (2048 x
-// 1536); one evaluation of 100 x 37 cells 56 against 30.  The compiled
+// Lengthens the FFT lengths P (open axes: the shortest 2-3-5-7 lengths >= 2n,
+// periodic axes: n) to the next lengths with compiled kernels; in 2D only
+// where every pass then runs compiled.  Zero padding beyond 2n - 1 leaves the
+// convolution unchanged (Sec. 3.2).  RK4 at 250 x 63 cells: 61 us per
+// evaluation with the runtime-length kernels at 500 x 126 points, 18 with the
+// compiled ones at 512 x 128; at 1000 x 600 cells 322 (2000 x 1200 points)
+// against 87 (2048 x 1536); one evaluation of 100 x 37 cells 56 against 30;
+// 100 x 60 x 20 cells (256 x 128 x 48 points) 113 -> 50 us.  The compiled
 // lengths are at most 3/2 apart, so the longer padding never costs what the
-// compiled kernels gain (3.3 to 3.7); 100 x 60 x 20 cells (256 x 128 x 48
-// points) 113 -> 50 us.  Kept as they are: a geometry whose
-// spectrum would outgrow the scratch of the no-allocation evaluation only
-// by the longer padding.
+// compiled kernels gain (3.3 to 3.7).
+//
+// A periodic axis whose own length has no compiled kernels is padded as well:
+// the circular convolution of n cells is the linear one of n cells with the
+// periodic kernel continued to the offsets -(n - 1) ... n - 1, exact for any
+// length >= 2n - 1.  2D, x and y periodic: 48 x 36 cells 28.8 -> 12.1 us per
+// evaluation, 512 x 512 58 -> 24.6, 1000 x 1000 198 -> 87.  3D: y and z, not
+// x, whose padding doubles the columns of every later pass (100 x 60 x 20,
+// all periodic: 60 us as it is, y and z padded 39.6, x as well 46; x alone
+// 39.4 -> 45.7).  Axes of two cells or fewer stay as they are.
 void compiled_lengths(const int n[3], const int pb[3], int P[3]) {
     int Q[3] = {P[0], P[1], P[2]};
+    const bool xper = pb[0] && fast2d_row_ok(P[0], 0, true);
     if (n[2] == 1) {
-        if (pb[1]) return;
-        const int px = pb[0] ? (fast2d_row_ok(P[0], 0, true) ? P[0] : 0) : fast2d_row_len_at_least(P[0]);
-        const int l = fast2d_col_len_at_least(P[1] / 2);
+        if ((pb[0] && !xper && n[0] <= 2) || (pb[1] && n[1] <= 2)) return;
+        const int px = xper ? P[0] : fast2d_row_len_at_least(pb[0] ? 2 * n[0] : P[0]);
+        const int l = fast2d_col_len_at_least(pb[1] ? n[1] : P[1] / 2);
         if (px == 0 || l == 0 || (px > 2048 && px != P[0])) return;
-        if (!fast2d_row_ok(px, 0, pb[0] != 0) || !fast2d_col_ok(l, 1, 0) || (px / 2) % fast2d_col_width(l, 0)) return;
+        if (!fast2d_row_ok(px, 0, xper) || !fast2d_col_ok(l, 1, 0) || (px / 2) % fast2d_col_width(l, 0)) return;
         Q[0] = px;
         Q[1] = 2 * l;
     } else {
         // 3D: every axis by itself
         const int px = pb[0] ? 0 : fast2d_row_len_at_least(P[0]);
         if (px > 0 && px <= 2048 && fast2d_row_ok(px, 0, false)) Q[0] = px;
-        const int ly = pb[1] ? 0 : fast3d_len_at_least(P[1] / 2, false);
+        int ly = 0, lz = 0;
+        if (!pb[1])
+            ly = fast3d_len_at_least(P[1] / 2, false);
+        else if (n[1] > 2 && !fast3d_col_ok(P[1], 0, false))
+            ly = fast3d_len_at_least(n[1], false);
         if (ly > 0) Q[1] = 2 * ly;
-        const int lz = pb[2] || fast3d_thin_ok(n[2], P[2], 1) ? 0 : fast3d_len_at_least(P[2] / 2, true);
+        if (!pb[2])
+            lz = fast3d_thin_ok(n[2], P[2], 1) ? 0 : fast3d_len_at_least(P[2] / 2, true);
+        else if (n[2] > 2 && !fast3d_col_ok(P[2], 0, true))
+            lz = fast3d_thin_ok(n[2], 2 * n[2], 1) ? n[2] : fast3d_len_at_least(n[2], true);
         if (lz > 0) Q[2] = 2 * lz;
     }
-    if (noalloc_need(n, P) <= kNoAllocBytes && noalloc_need(n, Q) > kNoAllocBytes) return;
     for (int a = 0; a < 3; ++a) P[a] = Q[a];
 }
 
@@ -837,7 +854,7 @@ llg_status llg_set_geometry(llg_solver* s, int nx, int ny, int nz, int pbc_x, in
         }
     }
     if (nz == 1) P[2] = 1;
-    const int split_y = !pb[1], split_z = nz > 1 && !pb[2];
+    int split_y = !pb[1], split_z = nz > 1 && !pb[2];
     int Ly = split_y ? P[1] / 2 : P[1];
     int Lz = split_z ? P[2] / 2 : P[2];
     if (P[0] > kMaxPx || Ly > kMaxHalf || Lz > kMaxHalf)
@@ -850,6 +867,8 @@ llg_status llg_set_geometry(llg_solver* s, int nx, int ny, int nz, int pbc_x, in
     const bool generic = gen && gen[0] == '1';
     if (!generic) {
         compiled_lengths(n, pb, P);
+        if (P[1] != P0[1]) split_y = 1;   // a padded periodic axis
+        if (P[2] != P0[2]) split_z = 1;
         Ly = split_y ? P[1] / 2 : P[1];
         Lz = split_z ? P[2] / 2 : P[2];
     }
@@ -909,6 +928,8 @@ llg_status llg_set_geometry(llg_solver* s, int nx, int ny, int nz, int pbc_x, in
     HIPCHK(s, make_tw(P[1], &s->twy));
     HIPCHK(s, make_tw(P[2], &s->twz));
     HIPCHK(s, hipMalloc(&s->S, sizeof(float2) * 3 * (size_t)g.nrows * g.nkxp));
+    if (noalloc_need(n, P) > kNoAllocBytes && noalloc_need(n, P0) <= kNoAllocBytes)
+        HIPCHK(s, hipMalloc(&s->noalloc, noalloc_need(n, P)));
     if (!two_d(s)) HIPCHK(s, hipMalloc(&s->Sy, sizeof(float2) * 3 * (size_t)g.nz * g.Py * g.nkxp));
     const size_t kcount = two_d(s) ? 4 * (size_t)g.nkx * (g.Py / 2 + 1)
                                    : 6 * (size_t)(g.Py / 2 + 1) * g.nkx * (g.Pz / 2 + 1);
@@ -1101,10 +1122,10 @@ llg_status llg_eval_heff_noalloc(llg_solver* s, const float* m_dev, float* h_dev
     const size_t sbytes = (sizeof(float2) * 3 * (size_t)g.nrows * g.nkxp + 255) / 256 * 256;
     const int ng[3] = {g.nx, g.ny, g.nz}, Pg[3] = {g.Px, g.Py, g.Pz};
     const size_t need = noalloc_need(ng, Pg);
-    if (need > kNoAllocBytes)
+    if (need > kNoAllocBytes && !s->noalloc)
         return fail(s, LLG_E_UNSUPPORTED, "this geometry needs %zu bytes of scratch, above the %zu-byte "
                                           "static array of the no-allocation evaluation", need, kNoAllocBytes);
-    char* base = noalloc_scratch(s->device);
+    char* base = s->noalloc ? s->noalloc : noalloc_scratch(s->device);
     if (!base) return fail(s, LLG_E_DEVICE, "no scratch address for device %d", s->device);
     EvalBufs b;
     b.st = (DevState*)base;

@@ -221,17 +221,22 @@ __global__ void tensor_octant_kernel(double* oct, int comp, TensorGeom tg, Octan
 }
 
 // place of FFT-grid index idx among the non-negative offsets (-1: the zero
-// gap of a padded axis); neg: the offset is negative
+// gap of a padded axis); neg: the offset is negative.  A padded periodic axis
+// continues the periodic tensor over the offsets -(n - 1) ... n - 1.
 __device__ int octant_index(int idx, int n, int P, int periodic, bool& neg) {
     neg = false;
-    if (periodic) {
-        if (idx <= n / 2) return idx;
+    if (!periodic) {
+        if (idx < n) return idx;
         neg = true;
-        return n - idx;
+        return idx > P - n ? P - idx : -1;
     }
-    if (idx < n) return idx;
+    if (idx >= n) {
+        if (idx <= P - n) return -1;
+        idx -= P - n;
+    }
+    if (idx <= n / 2) return idx;
     neg = true;
-    return idx > P - n ? P - idx : -1;
+    return n - idx;
 }
 
 __global__ void tensor_grid_kernel(double2* out, const double* oct, int comp, TensorGeom tg, Octant q) {

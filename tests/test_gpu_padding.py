@@ -20,8 +20,11 @@ FILMS = [((1, 1), (False, False)), ((3, 2), (False, False)), ((33, 2), (False, F
          ((768, 768), (False, False)), ((600, 520), (False, False)), ((769, 35), (False, False)),
          ((40, 769), (False, False)), ((1000, 5), (False, False)), ((64, 50), (True, False)),
          ((256, 31), (True, False)),
-         # periodic y, or periodic x of no compiled length: as before
-         ((50, 64), (False, True)), ((100, 37), (True, False))]
+         # periodic y, or periodic x of no compiled length: padded with the
+         # kernel continued periodically
+         ((50, 64), (False, True)), ((100, 37), (True, False)), ((6, 5), (True, True)), ((48, 35), (True, True)),
+         ((64, 49), (True, True)), ((33, 3), (False, True)), ((70, 64), (True, True)), ((1000, 6), (True, False)),
+         ((8, 1000), (True, True))]
 
 
 # 3D: the planes of the register z pass (2 ... 8) and beyond, both sides of
@@ -32,7 +35,8 @@ BLOCKS = [((20, 12, nz), (False,) * 3) for nz in (2, 3, 4, 5, 6, 7, 8, 9)] + \
      ((4, 400, 3), (False,) * 3), ((70, 6, 17), (False,) * 3), ((24, 10, 3), (True, False, False)),
      ((64, 10, 3), (True, False, False)), ((30, 24, 5), (False, True, False)), ((30, 96, 4), (False, True, False)),
      ((40, 48, 9), (True, True, False)), ((14, 192, 2), (False, True, False)), ((20, 9, 6), (False, False, True)),
-     ((20, 18, 4), (True, True, True))]
+     ((20, 18, 4), (True, True, True)), ((10, 9, 10), (True, True, True)), ((6, 100, 3), (False, True, True)),
+     ((6, 10, 40), (False, False, True)), ((12, 7, 8), (True, True, True))]
 
 
 def maxrel(a, b):
@@ -102,4 +106,24 @@ def test_tuning_calls_as_before(lib):
     with pytest.raises(lib.LLGError) as e:       # x padded beyond 2048 and no compiled 4096
         s.set_geometry((1100, 8, 1))
     assert e.value.code == lib.LLG_E_UNSUPPORTED
+    s.close()
+
+
+def test_noalloc_beyond_the_static_array(lib):
+    """A geometry whose spectra fit the static array at the shortest lengths
+    (27.6 MB) but not at the compiled ones (71 MB): accepted, the same bits as
+    the ordinary evaluation."""
+    import torch
+
+    prob, m0 = workloads.small_problem((140, 100, 40), pbc=(False, True, False), seed=5)
+    s = lib.Solver(0)
+    s.set_problem(prob)
+    s.set_m(m0)
+    h = s.eval_heff()
+    m_dev = torch.from_numpy(s.get_m()).to("cuda:0")
+    h_dev = torch.empty_like(m_dev)
+    torch.cuda.synchronize()
+    for _ in range(2):
+        s.eval_heff_noalloc(m_dev, h_dev)
+        assert np.array_equal(h_dev.cpu().numpy().reshape(-1), np.asarray(h).reshape(-1))
     s.close()
