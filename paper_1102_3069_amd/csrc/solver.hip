@@ -928,8 +928,10 @@ llg_status llg_set_geometry(llg_solver* s, int nx, int ny, int nz, int pbc_x, in
     HIPCHK(s, make_tw(P[1], &s->twy));
     HIPCHK(s, make_tw(P[2], &s->twz));
     HIPCHK(s, hipMalloc(&s->S, sizeof(float2) * 3 * (size_t)g.nrows * g.nkxp));
-    if (noalloc_need(n, P) > kNoAllocBytes && noalloc_need(n, P0) <= kNoAllocBytes)
+    if (noalloc_need(n, P) > kNoAllocBytes && noalloc_need(n, P0) <= kNoAllocBytes) {
         HIPCHK(s, hipMalloc(&s->noalloc, noalloc_need(n, P)));
+        HIPCHK(s, hipMemsetAsync(s->noalloc, 0, kNoAllocStateBytes, s->stream));
+    }
     if (!two_d(s)) HIPCHK(s, hipMalloc(&s->Sy, sizeof(float2) * 3 * (size_t)g.nz * g.Py * g.nkxp));
     const size_t kcount = two_d(s) ? 4 * (size_t)g.nkx * (g.Py / 2 + 1)
                                    : 6 * (size_t)(g.Py / 2 + 1) * g.nkx * (g.Pz / 2 + 1);
@@ -1131,8 +1133,14 @@ llg_status llg_eval_heff_noalloc(llg_solver* s, const float* m_dev, float* h_dev
     b.st = (DevState*)base;
     b.S = (float2*)(base + kNoAllocStateBytes);
     b.Sy = two_d(s) ? nullptr : (float2*)(base + kNoAllocStateBytes + sbytes);
-    hipLaunchKernelGGL(noalloc_state_kernel, dim3(1), dim3(64), 0, s->stream, b.st, (const DevState*)s->st);
-    HIPCHK(s, hipGetLastError());
+    // Of the state record a single evaluation reads the step counter of the
+    // thermal draw, and the buffer index and done flag, which are zero in the
+    // scratch from the start and stay so: without a thermal field the copy, a
+    // launch of its own (29.3 -> 26.6 us a call at 100 x 37 cells without it), is not needed
+    if (p.sig_th != 0.f) {
+        hipLaunchKernelGGL(noalloc_state_kernel, dim3(1), dim3(64), 0, s->stream, b.st, (const DevState*)s->st);
+        HIPCHK(s, hipGetLastError());
+    }
     if (p.demag_on) {
         FwdArgs fa = {};
         fa.m_in = bref(const_cast<float*>(m_dev));
