@@ -27,6 +27,52 @@ namespace llg {
 
 namespace {
 
+// Strides of a tile's LDS lines: sh between the halves of a column, sw between
+// columns.
+struct LineStrides {
+    int sh, sw;
+};
+
+// Bank conflicts (the extra passes of the worst bank) of the tile's accesses,
+// for 16 consecutive lanes on 16 banks of 8 bytes: the lane groups of P lanes
+// working on their lines, the columns of the transposing reads and writes, and
+// the two halves of the kernel product.  (Lines of L + 1 elements one after
+// another spread the columns but let the groups of a wavefront overlap: the z
+// pass of 256 x 256 x 64 cells 52.3 -> 48.3 us, its y passes 24.4 -> 23.5 and
+// 23.7 -> 22.6.  Counted over 32 lanes and banks the strides measured worse,
+// 50.0, 23.8 and 22.7.)
+constexpr int kBanks = 16;
+constexpr int t3_conflicts(int P, int TW, int H, LineStrides s) {
+    int cost = 0;
+    for (int pat = 0; pat < 3; ++pat) {
+        int cnt[kBanks] = {};
+        int worst = 0;
+        for (int l = 0; l < kBanks; ++l) {
+            const int g = l / P;
+            const int i = pat == 0 ? (g / H % TW) * s.sw + (g % H) * s.sh + l % P
+                        : pat == 1 ? (l % TW) * s.sw + l / TW
+                                   : (l % H) * s.sh + l / H;
+            const int c = ++cnt[i % kBanks];
+            worst = c > worst ? c : worst;
+        }
+        cost += worst - 1;
+    }
+    return cost;
+}
+
+// the shortest strides of fewest conflicts
+constexpr LineStrides t3_strides(int L, int P, int TW, int H) {
+    LineStrides best = {L, H * L};
+    int least = t3_conflicts(P, TW, H, best);
+    for (int sw = H * L; sw < H * L + kBanks; ++sw)
+        for (int sh = L; sh <= (H == 2 ? sw - L : L); ++sh) {
+            const LineStrides t = {sh, sw};
+            const int c = t3_conflicts(P, TW, H, t);
+            if (c < least) { least = c; best = t; }
+        }
+    return best;
+}
+
 // H = 2 halves (open axis) or 1 (periodic); E elements per lane; NC
 // components per block (3, or 1 with the component from the block index)
 template <int L, int E, int TW, int H, int NC>
@@ -36,14 +82,13 @@ struct Tile3 {
     static constexpr int NG = NC * TW * H;      // lane groups: component, column, half
     static constexpr int NT = NG * P;           // threads per block
     static_assert(64 % P == 0 && NT <= 1024 && NT % 64 == 0, "groups fill whole wavefronts");
-    // one LDS line per group, long enough to be that group's FFT scratch;
-    // an odd stride spreads the rows of the tile over the banks
-    static constexpr int LS = LfScratch<L>::size + 1;
+    // one LDS line per group, which is that group's FFT scratch
+    static constexpr LineStrides S = t3_strides(L, P, TW, H);
     using F = LaneFFT<L, E, H, float2>;
     static constexpr int O_TWS = H * L;         // after the twiddles exp(-2 pi i m / (H L))
     static constexpr int O_X = O_TWS + F::TWS_ALLOC;   // after the stage twiddle tables
-    static constexpr int bytes() { return (O_X + NG * LS) * 8; }
-    static __device__ __forceinline__ int line(int c, int w, int h) { return ((c * TW + w) * H + h) * LS; }
+    static constexpr int bytes() { return (O_X + NC * TW * S.sw) * 8; }
+    static __device__ __forceinline__ int line(int c, int w, int h) { return (c * TW + w) * S.sw + h * S.sh; }
 };
 
 // kernel spectrum entries at (kx, ka along the pass, ko along y): mirror
