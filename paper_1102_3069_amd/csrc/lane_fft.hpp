@@ -170,7 +170,6 @@ template <int L, int E, int TM, typename C>
 struct LaneFFT {
     static constexpr int P = L / E;
     static constexpr int NS = lf_nstages(L, E);
-    static constexpr int SCRATCH = LfScratch<L>::size;   // elements per group
     // swizzle shifts: plans of radix 4 and below (E not a multiple of 8) take
     // bits 2 and 3, which spread their stride-2 and stride-4 stage stores
     // over the banks (bank conflicts of the 1024-point rows 104448 -> 6144
