@@ -82,6 +82,9 @@ struct Phys {
     int demag_on;
 };
 
+// an adaptive run tells the host its attempt count every so many attempts
+constexpr int kPublishEvery = 3;
+
 // Integrator state kept on the device so that the adaptive controller and
 // the buffer swaps run without the host.
 struct DevState {

@@ -516,12 +516,14 @@ llg_status restore_done(llg_solver* s, int was) {
 // host keeps kAhead graphs queued, so the device never waits for the host,
 // and at most kAhead - 1 graphs are launched past the end (they do nothing:
 // every kernel of a step returns while the flag is set, but each costs its
-// launches; chunks of eight wasted up to fifteen: 69 attempts at 512 x 512
-// 13.57 -> 13.20 ms, 10 at 2048 x 2048 27.24 -> 26.90 ms).  Should the stream run dry
+// launches; chunks of eight wasted up to fifteen).  Twice the publishing
+// interval keeps three or more queued: 69 attempts at 512 x 512 12.81 -> 12.65
+// ms against every attempt published and three ahead, 10 at 2048 x 2048 26.35
+// -> 26.46; every fourth and twelve ahead 13.16 and 26.63.  Should the stream run dry
 // without the expected count (a run that ended on a non-finite value between
 // two attempts), the wait below ends too.
 llg_status launch_until_done(llg_solver* s, hipGraphExec_t exec, long long base, long long max_launches) {
-    constexpr long long kAhead = 3;
+    constexpr long long kAhead = 2 * kPublishEvery;
     volatile unsigned long long* progress = s->progress;
     *progress = (unsigned long long)base << 1;
     long long launched = 0;
