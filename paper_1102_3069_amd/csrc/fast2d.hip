@@ -582,15 +582,9 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
     const float* m0 = resolve(sa.m0, cur);
     float* mo = resolve(sa.m_out, cur);
     float* ko = resolve(sa.k_out, cur);
-    // staged row rq holds grid row rb - 1 + rq; NAT (3D): the halo rows serve
-    // only as in-plane neighbours, the periodic y wrap and the z neighbours
-    // come from global memory
-    auto staged_row = [&](int rq, bool& ok) {
-        int row = rb - 1 + rq;
-        ok = row >= 0 && row < g.nrows;
-        if (!NAT && g.pbc[1]) { row = row < 0 ? row + ny : (row >= ny ? row - ny : row); ok = true; }
-        return row;
-    };
+    // staged row rq holds grid row rb - 1 + rq (staged_row); NAT (3D): the
+    // halo rows serve only as in-plane neighbours, the periodic y wrap and the
+    // z neighbours come from global memory
     // 16-byte loads where every (row, component) run of nx floats starts
     // 16-byte aligned, else single values, into the same registers; BIG: no
     // staged rows (the per-cell work reads m from global memory)
@@ -607,7 +601,7 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
     };
     auto row_src = [&](int rc, bool& ok) {
         const int rq = rc / 3, c = rc - 3 * rq;
-        const int row = staged_row(rq, ok);
+        const int row = staged_row(rb - 1 + rq, g.nrows, !NAT && g.pbc[1], ok);
         return mi + ((uint32_t)c * (uint32_t)cs + (uint32_t)row * (uint32_t)nx);   // (3 ncells < 2^32)
     };
     constexpr int CR = ROW1 ? ITR : 8;           // 16-byte units per round

@@ -206,6 +206,19 @@ __device__ __forceinline__ int touch_args(int x) {
     return touch_lines<BYTES>((karg_ptr)__builtin_amdgcn_kernarg_segment_ptr(), x);
 }
 
+// The grid row that a block of row transforms stages for row `row` = rb - 1,
+// ..., rb + 2 RP of nrows (its own rows rb ... rb + 2 RP - 1 and one halo row
+// each side); ok is false where it stages zeros instead.  wrap (2D films
+// periodic in y): the halo of the first and the last row is the other one.
+// A ragged last block also stages rows past its halo, which no cell reads: on
+// films of fewer rows than a block has, those lie beyond a second period.
+__host__ __device__ inline int staged_row(int row, int nrows, bool wrap, bool& ok) {
+    if (wrap && row == -1) row = nrows - 1;
+    else if (wrap && row == nrows) row = 0;
+    ok = row >= 0 && row < nrows;
+    return row;
+}
+
 enum RowMode {
     ROW_EVAL = 0,    // write H_eff (A/m)
     ROW_STAGE = 1,   // k_s, next stage input, its forward x transform
