@@ -369,6 +369,10 @@ hipError_t launch_col_group(int L, int var, const FilmCol* films, const int2* ma
 hipError_t launch_ctrl_dp45_group(DevState* states, int nfilms, hipStream_t s);
 hipError_t launch_ctrl_fixed_group(DevState* states, int nfilms, int evals, hipStream_t s);
 
+// ---- padding rule (solver.hip) ---------------------------------------------------
+// P: the shortest FFT lengths in, the lengths to run out (n cells, pb: periodic)
+void compiled_lengths(const int n[3], const int pb[3], int P[3]);
+
 // ---- demag tensor (tensor.hip) --------------------------------------------------
 struct TensorGeom {
     int n[3];

@@ -229,26 +229,51 @@ size_t noalloc_need(const int n[3], const int P[3]) {
     return kNoAllocStateBytes + (row * (size_t)n[1] * n[2] + 255) / 256 * 256 + sy;
 }
 
+}  // namespace
+
 // Lengthens the FFT lengths P (open axes: the shortest 2-3-5-7 lengths >= 2n,
-// periodic axes: n) to the next lengths with compiled kernels; in 2D only
-// where every pass then runs compiled.  Zero padding beyond 2n - 1 leaves the
-// convolution unchanged (Sec. 3.2).  RK4 at 250 x 63 cells: 61 us per
-// evaluation with the runtime-length kernels at 500 x 126 points, 18 with the
-// compiled ones at 512 x 128; at 1000 x 600 cells 322 (2000 x 1200 points)
-// against 87 (2048 x 1536); one evaluation of 100 x 37 cells 56 against 30;
-// 100 x 60 x 20 cells (256 x 128 x 48 points) 113 -> 50 us.  The compiled
-// lengths are at most 3/2 apart, so the longer padding never costs what the
-// compiled kernels gain (3.3 to 3.7).
+// periodic axes: n) to the next lengths with compiled kernels.  Zero padding
+// beyond 2n - 1 leaves the convolution unchanged (Sec. 3.2).
+//
+// 2D: only where every pass then runs compiled.  RK4 at 250 x 63 cells: 61 us
+// per evaluation with the runtime-length kernels at 500 x 126 points, 18 with
+// the compiled ones at 512 x 128; at 1000 x 600 cells 322 (2000 x 1200 points)
+// against 87 (2048 x 1536); one evaluation of 100 x 37 cells 56 against 30.
+// The compiled lengths are up to twice the shortest (rows 66 ... 128 points,
+// columns 2060 ... 4096), 32 times for a few cells along x, and it paid all
+// the same: 1000 x 1030 cells (2048 x 4096 points) 574 -> 148, 5 x 1030 89 ->
+// 28, 2 x 5 20 -> 15.
 //
 // A periodic axis whose own length has no compiled kernels is padded as well:
 // the circular convolution of n cells is the linear one of n cells with the
 // periodic kernel continued to the offsets -(n - 1) ... n - 1, exact for any
 // length >= 2n - 1.  2D, x and y periodic: 48 x 36 cells 28.8 -> 12.1 us per
-// evaluation, 512 x 512 58 -> 24.6, 1000 x 1000 198 -> 87.  3D: y and z, not
-// x, whose padding doubles the columns of every later pass (100 x 60 x 20,
-// all periodic: 60 us as it is, y and z padded 39.6, x as well 46; x alone
-// 39.4 -> 45.7).  Axes of two cells or fewer stay as they are.
-void compiled_lengths(const int n[3], const int pb[3], int P[3]) {
+// evaluation, 270 x 270 (768 x 768 points, eight times as many) 50 -> 27,
+// 1000 x 1000 198 -> 87.  3D: y and z, not x, whose padding doubles the
+// columns of every later pass (100 x 60 x 20, all periodic: 60 us as it is, y
+// and z padded 39.6, x as well 46; x alone 39.4 -> 45.7); y and z both just
+// above a compiled length: 256 x 270 x 135 3340 -> 2000, 256 x 18 x 10 40 ->
+// 35.  Axes of two cells or fewer stay as they are.
+//
+// 3D, every pass compiled: 100 x 60 x 20 cells (256 x 128 x 48 points) 113 ->
+// 50 us, and blocks of few cells along x, whose columns grow most, are faster
+// than at the shortest lengths, too (4 x 100 x 20 63 -> 36, 2 x 256 x 130 236
+// -> 178).  Where a column pass keeps the runtime-length kernel (more than 256
+// planes, or more than 512 cells along y), every column that the padding of
+// another axis adds costs that pass its full price, so the other axes are
+// padded only as far as their own compiled passes pay for it.  Measured with z
+// at runtime length, us per evaluation unpadded and padded:
+//   y  300 x 20 x 270  (40 -> 48)    1306  1418      64 x 40 x 300 (80 -> 96)   600  555
+//      300 x 28 x 270  (56 -> 64)    1831  1900      64 x 17 x 300 (36 -> 48)   270  299
+//   x  125 x 40 x 300  (250 -> 256)  1075  1061     110 x 40 x 300 (224 -> 256)  978 1055
+//      650 x 40 x 300  (1300 -> 1536) 6935 6434     540 x 40 x 300 (1080 -> 1536) 5588 6431
+//      4 x 600 x 300   (8 -> 64)     1514  4764
+// and with y alone at runtime length:
+//   x  125 x 600 x 20  (250 -> 256)   518   520     100 x 600 x 20 (200 -> 256)  436  513
+//      540 x 600 x 20  (1080 -> 1536) 3365 3130      10 x 1000 x 20 (20 -> 64)   204  235
+//      24 x 600 x 4    (48 -> 64)      78    65      80 x 600 x 2   (160 -> 192)  75   71
+// (the last two do not fill the chip, so their extra columns are free).
+void llg::compiled_lengths(const int n[3], const int pb[3], int P[3]) {
     int Q[3] = {P[0], P[1], P[2]};
     const bool xper = pb[0] && fast2d_row_ok(P[0], 0, true);
     if (n[2] == 1) {
@@ -260,23 +285,31 @@ void compiled_lengths(const int n[3], const int pb[3], int P[3]) {
         Q[0] = px;
         Q[1] = 2 * l;
     } else {
-        // 3D: every axis by itself
-        const int px = pb[0] ? 0 : fast2d_row_len_at_least(P[0]);
-        if (px > 0 && px <= 2048 && fast2d_row_ok(px, 0, false)) Q[0] = px;
-        int ly = 0, lz = 0;
-        if (!pb[1])
-            ly = fast3d_len_at_least(P[1] / 2, false);
-        else if (n[1] > 2 && !fast3d_col_ok(P[1], 0, false))
-            ly = fast3d_len_at_least(n[1], false);
-        if (ly > 0) Q[1] = 2 * ly;
+        // z, then y, then x: each by what the passes of the ones before run
+        int lz = 0, ly = 0;
         if (!pb[2])
             lz = fast3d_thin_ok(n[2], P[2], 1) ? 0 : fast3d_len_at_least(P[2] / 2, true);
         else if (n[2] > 2 && !fast3d_col_ok(P[2], 0, true))
             lz = fast3d_thin_ok(n[2], 2 * n[2], 1) ? n[2] : fast3d_len_at_least(n[2], true);
         if (lz > 0) Q[2] = 2 * lz;
+        const bool zfast = lz > 0 || (pb[2] ? fast3d_col_ok(P[2], 0, true) : fast3d_thin_ok(n[2], P[2], 1));
+        if (!pb[1])
+            ly = fast3d_len_at_least(P[1] / 2, false);
+        else if (n[1] > 2 && !fast3d_col_ok(P[1], 0, false))
+            ly = fast3d_len_at_least(n[1], false);
+        if (ly > 0 && !zfast && 2 * ly > (P[1] < 64 ? 1.1 : 1.25) * P[1]) ly = 0;
+        if (ly > 0) Q[1] = 2 * ly;
+        const bool yfast = ly > 0 || (pb[1] && fast3d_col_ok(P[1], 0, false));
+        const int px = pb[0] ? 0 : fast2d_row_len_at_least(P[0]);
+        const bool few = (px / 2 + 1) * n[2] <= 200;   // columns of the y passes
+        const bool pays = (yfast && zfast) || px <= 1.05 * P[0] || (P[0] > 1024 && (zfast || px <= 1.2 * P[0])) ||
+                          (zfast && few);
+        if (pays && px > 0 && px <= 2048 && fast2d_row_ok(px, 0, false)) Q[0] = px;
     }
     for (int a = 0; a < 3; ++a) P[a] = Q[a];
 }
+
+namespace {
 
 Phys make_phys(const llg_solver* s, double dt_thermal) {
     Material m;

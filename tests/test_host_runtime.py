@@ -1,6 +1,7 @@
 """Host-side parts of the library that the GPU tests cannot check safely, run
 without a GPU under the address and undefined-behaviour sanitizers: the rows
-that the inverse row kernel reads."""
+that the inverse row kernel reads, and the FFT lengths that a geometry is
+padded to."""
 import os
 import subprocess
 
@@ -27,7 +28,7 @@ def build(name, *extra):
         cmd = [HIPCC, "--offload-arch=gfx950", "-O1", "-g", "-std=c++17",
                "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
                "-Xarch_host", "-fno-sanitize-recover=all",
-               "-I", os.path.join(ROOT, "include"), "-I", CSRC, *extra, os.path.join(host, name + ".hip"), "-o", out]
+               "-I", os.path.join(ROOT, "include"), "-I", CSRC, os.path.join(host, name + ".hip"), *extra, "-o", out]
         r = subprocess.run(cmd, capture_output=True, text=True)
         assert r.returncode == 0, r.stderr[-4000:]
     return out
@@ -42,3 +43,13 @@ def run(out, *args):
 
 def test_staged_rows_stay_inside_the_film():
     assert "staged rows ok" in run(build("host_rows"))
+
+
+def test_padded_lengths(tmp_path):
+    """Linked with the library as it is built."""
+    pkg = os.path.dirname(OBJ)
+    lib = os.path.join(pkg, "libllg.so")
+    if not os.path.exists(lib):
+        import __graft_entry__
+        __graft_entry__.build()
+    assert "padding ok" in run(build("host_padding", "-L" + pkg, "-l:libllg.so", "-Wl,-rpath," + pkg))
