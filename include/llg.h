@@ -280,7 +280,8 @@ llg_status llg_kernel_bytes(llg_solver *s, double *bytes_out, int n_kinds);
  * The 2D path has two compiled variants (elements per lane, hence lanes and
  * wavefronts per transform) for every row length and every column length.
  * A process-wide table holds the default variant of each length (variant 0
- * at start).  llg_set_geometry and llg_batch_create copy the defaults of
+ * at start; 3D rows of up to 1024 points whose length no tuning call has set
+ * take the first variant of two frequency classes).  llg_set_geometry and llg_batch_create copy the defaults of
  * their lengths (variant 0 where the default cannot serve the geometry);
  * a solver or batch then keeps its variants until its own llg_autotune,
  * llg_set_variants, llg_batch_autotune or llg_batch_set_variant call,

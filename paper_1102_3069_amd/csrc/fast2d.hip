@@ -14,6 +14,7 @@
 // group, the two halves of a zero-padded axis meet in LDS at the end.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstdlib>
 #include <map>
@@ -1399,7 +1400,8 @@ struct Fast2dPart {
 #if FAST2D_PART == 0
 namespace {
 
-// the variant table: lengths up to 4096 in steps of 32
+// the variant table: lengths up to 4096 in steps of 32; rows hold 1 + the
+// variant, 0 until a tuning call has set it
 std::atomic<int> g_row_var[129], g_col_var[129];
 int slot(int len) { return (len % 32 == 0 && len >= 32 && len <= 4096) ? len / 32 : 0; }
 
@@ -1419,7 +1421,8 @@ hipError_t any_part(F f) {
 // ---------------------------------------------------------------------------
 // dispatch
 // ---------------------------------------------------------------------------
-int fast2d_row_variant(int Px) { return g_row_var[slot(Px)].load(); }
+int fast2d_row_variant(int Px) { return std::max(0, g_row_var[slot(Px)].load() - 1); }
+bool fast2d_row_variant_set(int Px) { return g_row_var[slot(Px)].load() != 0; }
 
 // tile width of the 2D spectrum (log2); LLG_TILE_LOG2 overrides it for
 // layout experiments
@@ -1431,7 +1434,7 @@ int fast2d_tile_shift() {
 int fast2d_col_variant(int L) { return g_col_var[slot(L)].load(); }
 bool fast2d_set_row_variant(int Px, int var, bool xper) {
     if (!fast2d_row_ok(Px, var, xper)) return false;
-    g_row_var[slot(Px)].store(var);
+    g_row_var[slot(Px)].store(var + 1);
     return true;
 }
 bool fast2d_set_col_variant(int L, int var) {
@@ -1441,7 +1444,7 @@ bool fast2d_set_col_variant(int L, int var) {
 }
 bool fast2d_set_variants(int Px, int rv, int L, int cv, bool xper) {
     if (!fast2d_row_ok(Px, rv, xper) || !fast2d_col_ok(L, 1, cv)) return false;
-    g_row_var[slot(Px)].store(rv);
+    g_row_var[slot(Px)].store(rv + 1);
     g_col_var[slot(L)].store(cv);
     return true;
 }

@@ -318,6 +318,7 @@ hipError_t launch_fft_test(float2* data, int n, int batch, const FftPlan& pl, co
 bool fast2d_row_ok(int Px, int var = -1, bool xper = false);
 bool fast2d_col_ok(int L, int split, int var = -1);
 int fast2d_row_variant(int Px);
+bool fast2d_row_variant_set(int Px);   // by a tuning call
 int fast2d_tile_shift();
 int fast2d_col_variant(int L);
 bool fast2d_set_variants(int Px, int row_var, int L, int col_var, bool xper = false);

@@ -936,8 +936,9 @@ llg_status llg_set_geometry(llg_solver* s, int nx, int ny, int nz, int pbc_x, in
     // llg_set_variants, whatever later calls do to the table
     g.rvar = fast2d_row_variant(P[0]);
     if (!fast2d_row_ok(P[0], g.rvar, nx == P[0])) g.rvar = 0;
-    // 3D: rows of up to 1024 points in two classes (four measured slower)
-    if (nz > 1 && P[0] <= 1024)
+    // 3D rows of up to 1024 points whose variant no tuning call has set: two
+    // classes (forward rows of 256 x 256 x 64 cells 21 us, in four classes 34)
+    if (nz > 1 && P[0] <= 1024 && !fast2d_row_variant_set(P[0]))
         for (int v = 0; v < 2; ++v)
             if (fast2d_row_classes(P[0], v) == 2 && fast2d_row_ok(P[0], v, nx == P[0])) {
                 g.rvar = v;
