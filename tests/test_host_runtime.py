@@ -1,7 +1,7 @@
 """Host-side parts of the library that the GPU tests cannot check safely, run
 without a GPU under the address and undefined-behaviour sanitizers: the rows
-that the inverse row kernel reads, and the FFT lengths that a geometry is
-padded to."""
+that the inverse row kernel reads, the FFT lengths that a geometry is padded
+to, and the batched runtime's handling of buffers, streams and graphs."""
 import os
 import subprocess
 
@@ -45,11 +45,23 @@ def test_staged_rows_stay_inside_the_film():
     assert "staged rows ok" in run(build("host_rows"))
 
 
-def test_padded_lengths(tmp_path):
-    """Linked with the library as it is built."""
+def library():
+    """Link arguments for the library as it is built."""
     pkg = os.path.dirname(OBJ)
-    lib = os.path.join(pkg, "libllg.so")
-    if not os.path.exists(lib):
+    if not os.path.exists(os.path.join(pkg, "libllg.so")):
         import __graft_entry__
         __graft_entry__.build()
-    assert "padding ok" in run(build("host_padding", "-L" + pkg, "-l:libllg.so", "-Wl,-rpath," + pkg))
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    return ["-L" + pkg, "-l:libllg.so", "-Wl,-rpath," + pkg, "-L" + os.path.join(rocm, "lib"), "-lrocprofiler-sdk-roctx"]
+
+
+def test_padded_lengths():
+    assert "padding ok" in run(build("host_padding", *library()))
+
+
+def test_batches_run_to_their_end_again_and_again():
+    """Three batches of 64 uneven films, set anew and run to t_end 40 times, with
+    fixed steps, tuning and re-creation in between, on a stand-in for the HIP
+    runtime: no access outside an allocation, no use after a release, no broken
+    rule of captures, every resource given back."""
+    assert "batch ok" in run(build("host_batch", *library()))
