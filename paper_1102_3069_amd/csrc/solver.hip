@@ -642,8 +642,13 @@ llg_status enqueue_fixed_step(llg_solver* s, const Tableau& t, const Phys& p) {
 // Long runs of fixed steps replay a graph of kStepsPerGraph steps with one
 // controller launch at its end: at 32 x 32 cells a step is a chain of five
 // launches of 4 to 8 us each, and the controller one of them (50 Heun steps
-// 1735 -> 1476 us).  A run must be at least twice that long to pay for the
-// longer capture.
+// 1735 -> 1476 us).  Its capture takes longer than that of a single step: a
+// call of 16 RK4 steps at 64 x 64 x 16 cells whose dt is new each time takes
+// 2157 us with it and 2084 without, of 24 steps 3066 and 3073, of 32 3998 and
+// 4051; 16 Heun steps 1110 and 1122; reused, 16 RK4 steps take 1863 and 2016.
+// So it is captured for calls of two graphs' worth of steps where a step has
+// at most two stages or its graph is there from an earlier call, else of
+// three.
 constexpr int kStepsPerGraph = 8;
 llg_status enqueue_fixed_chunk(llg_solver* s, const Tableau& t, const Phys& p) {
     return enqueue_fixed_steps(s, t, p, kStepsPerGraph);
@@ -1219,14 +1224,15 @@ llg_status llg_step(llg_solver* s, llg_method method, double dt, int64_t nsteps)
         if ((rc = launch_fwd_plain(s, 1)) != LLG_OK) return rc;
     const Tableau t = tf;
     int64_t left = nsteps;
-    if (nsteps >= 2 * kStepsPerGraph && (!s->gfixn.exec || s->gfixn.method != (int)method || s->gfixn.dt != dt)) {
+    auto serves = [&](const Graph& g) { return g.exec && g.method == (int)method && g.dt == dt; };
+    if (nsteps >= (serves(s->gfix) || t.S <= 2 ? 2 : 3) * kStepsPerGraph && !serves(s->gfixn)) {
         if ((rc = capture(s, s->gfixn, enqueue_fixed_chunk, t, p)) != LLG_OK) return rc;
         s->gfixn.method = (int)method;
         s->gfixn.dt = dt;
     }
-    if (s->gfixn.exec && s->gfixn.method == (int)method && s->gfixn.dt == dt)
+    if (serves(s->gfixn))
         for (; left >= kStepsPerGraph; left -= kStepsPerGraph) HIPCHK(s, hipGraphLaunch(s->gfixn.exec, s->stream));
-    if (left > 0 && (!s->gfix.exec || s->gfix.method != (int)method || s->gfix.dt != dt)) {
+    if (left > 0 && !serves(s->gfix)) {
         if ((rc = capture(s, s->gfix, enqueue_fixed_step, t, p)) != LLG_OK) return rc;
         s->gfix.method = (int)method;
         s->gfix.dt = dt;
