@@ -465,7 +465,10 @@ typedef struct {
 } llg_sur_stats;
 
 /* A network for films of H x W cells and batches of up to max_batch states;
- * parameters must be set before use. */
+ * parameters must be set before use.  Allocates all it will use: about 1.5 KB
+ * per cell of max_batch states, and the weight gradients' partial sums (of all
+ * six layers up to 256 MiB in total, else of one layer: 36 KiB per image or
+ * more). */
 llg_status  llg_sur_create(int device, int H, int W, int max_batch, llg_sur **out);
 void        llg_sur_destroy(llg_sur *s);
 const char *llg_sur_last_error(const llg_sur *s);

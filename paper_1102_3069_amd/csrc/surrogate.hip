@@ -282,6 +282,12 @@ constexpr int WG_LA = 72;          // LDS row strides (u16), 16-byte aligned row
 constexpr int WG_LG = 88;          // gradient 8 (the last one the pixel before) + 64 + 16 (the first the pixel after)
 constexpr int WG_ROUND = 3 * 256;  // blocks the card holds at a time
 constexpr int WG_SEG = 64;         // segments of the first reduction stage
+// The partials of all layers are held for one reduction at the end (two
+// launches instead of twelve) up to this many bytes: 170 MB at 16 states of
+// 256 x 256 or more.  Small images in large batches have more blocks than one
+// round, at least one per image; beyond the limit each layer is reduced before
+// the next one takes its place.
+constexpr size_t WG_HELD = (size_t)256 << 20;
 constexpr int NWG = 9 * CH * CH;   // weight-gradient entries of one layer
 
 // channels 8 cg .. 8 cg + 7 of pixel x of row y (zero outside the image)
@@ -683,7 +689,8 @@ struct llg_sur {
     float* g = nullptr;                        // gradient w.r.t. a layer's output (float, 32 ch)
     u16* gz = nullptr;                         // gradient w.r.t. pre-activation (bf16)
     u16* gz2 = nullptr;                        // the same for the layer below (ping-pong)
-    float* part_w = nullptr;                   // per-block weight gradients of every layer
+    int wslots = NL;                           // layers whose per-block gradients are held at a time (NL or 1)
+    float* part_w = nullptr;                   // per-block weight gradients
     float* part_b = nullptr;
     float* part2 = nullptr;                    // first-stage sums of the weight-gradient reduction
     float* part_l = nullptr;
@@ -790,6 +797,16 @@ LayerSet layer_set(const llg_sur* s, float* w) {
     return ls;
 }
 
+// layer l alone, as the first of a set to reduce into
+LayerSet one_layer(int l, float* w, float* b) {
+    LayerSet ls = {};
+    ls.cin[0] = CIN[l];
+    ls.cout[0] = COUT[l];
+    ls.w[0] = w;
+    ls.b[0] = b;
+    return ls;
+}
+
 // an Adam step (lr > 0) and the bf16 weights
 llg_status update_pack(llg_sur* s, float lr, float c1, float c2) {
     hipLaunchKernelGGL(update_pack_kernel, dim3((NWG + CH + 255) / 256, 1, NL), dim3(256), 0, s->stream,
@@ -883,9 +900,10 @@ llg_status llg_sur_create(int device, int H, int W, int max_batch, llg_sur** out
     SCHK(s, hipMalloc(&s->gz2, npx * CH * 2));
     int maxblk = 0;
     for (int n = 1; n <= max_batch; ++n) maxblk = std::max(maxblk, wg_blocks(s, n));
-    SCHK(s, hipMalloc(&s->part_w, (size_t)NL * maxblk * NWG * 4));
-    SCHK(s, hipMalloc(&s->part_b, (size_t)NL * maxblk * CH * 4));
-    SCHK(s, hipMalloc(&s->part2, (size_t)NL * WG_SEG * (NWG + CH) * 4));
+    s->wslots = (size_t)NL * maxblk * NWG * 4 <= WG_HELD ? NL : 1;
+    SCHK(s, hipMalloc(&s->part_w, (size_t)s->wslots * maxblk * NWG * 4));
+    SCHK(s, hipMalloc(&s->part_b, (size_t)s->wslots * maxblk * CH * 4));
+    SCHK(s, hipMalloc(&s->part2, (size_t)s->wslots * WG_SEG * (NWG + CH) * 4));
     SCHK(s, hipMalloc(&s->part_l, ((size_t)H * W + 255) / 256 * max_batch * 4));
     SCHK(s, hipHostMalloc(&s->loss, sizeof(float)));
     SCHK(s, hipMalloc(&s->dm_in, npx * 3 * 4));
@@ -1001,8 +1019,12 @@ llg_status llg_sur_train_step(llg_sur* s, const float* m_in, const float* m_targ
     u16* gcur = s->gz;    // gradient at layer l's pre-activation
     u16* gnext = s->gz2;
     for (int l = NL - 1; l >= 0; --l) {
-        launch_wgrad(s, gcur, s->act[l], batch, l);
+        launch_wgrad(s, gcur, s->act[l], batch, s->wslots > 1 ? l : 0);
         SCHK(s, hipGetLastError());
+        if (s->wslots == 1) {
+            launch_wgrad_reduce(s, batch, 1, one_layer(l, s->grads + s->woff[l], s->grads + s->boff[l]));
+            SCHK(s, hipGetLastError());
+        }
         if (l > 0) {
             // data gradient: the same convolution with flipped, transposed
             // weights, times SiLU'(z) of layer l - 1 (every hidden layer has
@@ -1013,8 +1035,10 @@ llg_status llg_sur_train_step(llg_sur* s, const float* m_in, const float* m_targ
             std::swap(gcur, gnext);
         }
     }
-    launch_wgrad_reduce(s, batch, NL, layer_set(s, s->grads));
-    SCHK(s, hipGetLastError());
+    if (s->wslots > 1) {
+        launch_wgrad_reduce(s, batch, NL, layer_set(s, s->grads));
+        SCHK(s, hipGetLastError());
+    }
     if (lr > 0.f) {
         s->adam_t += 1;
         const float c1 = 1.0f - powf(0.9f, (float)s->adam_t), c2 = 1.0f - powf(0.999f, (float)s->adam_t);
@@ -1101,12 +1125,7 @@ llg_status llg_sur_conv_check(llg_sur* s, int layer, const float* x, const float
         SCHK(s, hipGetLastError());
         launch_wgrad(s, s->gz, s->act[0], batch, 0);
         SCHK(s, hipGetLastError());
-        LayerSet ls = {};
-        ls.cin[0] = CIN[layer];
-        ls.cout[0] = COUT[layer];
-        ls.w[0] = dgw;
-        ls.b[0] = dgb;
-        launch_wgrad_reduce(s, batch, 1, ls);
+        launch_wgrad_reduce(s, batch, 1, one_layer(layer, dgw, dgb));
         SCHK(s, hipGetLastError());
         launch_conv(s, s->gz, s->wtr[layer], nullptr, s->z[1], nullptr, nullptr, nullptr, nullptr, batch, 0);
         SCHK(s, hipGetLastError());
