@@ -13,10 +13,13 @@ ROUND = 5 * 256      # forward blocks the card holds at a time
 
 
 def block_rows(N, H, W):
-    """Rows of a forward block (at most 24, whole rounds of blocks)."""
+    """Rows of a forward block (at most 24, whole rounds of blocks, an image's
+    rows dealt evenly over its blocks)."""
     rb = (W + 63) // 64 * H * N
     rounds = -(-rb // (ROUND * 24))
-    return -(-rb // (ROUND * rounds)), rounds
+    most = -(-rb // (ROUND * rounds))
+    parts = -(-H // most)
+    return -(-H // parts), rounds
 
 
 # (layer, N, H, W): rows per forward block, the last block's, rounds
@@ -25,9 +28,10 @@ def block_rows(N, H, W):
     (2, 128, 31, 66, 7, 3, 1),       # two column tiles
     (0, 160, 77, 5, 10, 7, 1),
     (5, 160, 77, 5, 10, 7, 1),
-    (1, 240, 69, 3, 13, 4, 1),       # as 16 states of 256 x 256
-    (2, 316, 97, 2, 24, 1, 1),       # the longest block, a last one of one row
-    (2, 160, 211, 3, 14, 1, 2),      # two rounds
+    (1, 64, 256, 3, 13, 9, 1),       # as 16 states of 256 x 256
+    (2, 320, 95, 2, 24, 23, 1),      # the longest block
+    (2, 160, 211, 3, 14, 1, 2),      # two rounds, a last block of one row
+    (0, 1111, 12, 12, 6, 6, 1),      # 11 rows fit, dealt evenly
 ])
 def test_conv_many_rows(lib, layer, N, H, W, rows, last, rounds):
     """Forward, weight, bias and input gradients of one layer against the FP64
