@@ -306,6 +306,9 @@ void llg::compiled_lengths(const int n[3], const int pb[3], int P[3]) {
                           (zfast && few);
         if (pays && px > 0 && px <= 2048 && fast2d_row_ok(px, 0, false)) Q[0] = px;
     }
+    // (a launch has fewer than 2^32 threads, and the tensor is built with one per
+    // point: 980 x 1000 x 540 cells have 0.99 times as many at the shortest lengths)
+    if ((long long)Q[0] * Q[1] * Q[2] >= 1LL << 32) return;
     for (int a = 0; a < 3; ++a) P[a] = Q[a];
 }
 

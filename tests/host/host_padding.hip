@@ -41,6 +41,8 @@ int main() {
     expect(100, 600, 20, 200, 1200, 48);
     expect(540, 600, 20, 1536, 1200, 48);
     expect(24, 600, 4, 64, 1200, 8);
+    // as many points as a launch may have threads: as it is
+    expect(980, 1000, 540, 1960, 2000, 1080);
     // every pass compiled
     expect(4, 100, 20, 64, 256, 48);
     expect(100, 60, 20, 256, 128, 48);
