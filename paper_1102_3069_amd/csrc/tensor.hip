@@ -208,14 +208,16 @@ struct Octant {
     int m[3];
 };
 
-__global__ void tensor_octant_kernel(double* oct, int comp, TensorGeom tg, Octant q) {
+// components comp0 + blockIdx.y
+__global__ void tensor_octant_kernel(double* oct, int comp0, TensorGeom tg, Octant q) {
+    const int comp = comp0 + (int)blockIdx.y;
     const long long tot = (long long)q.m[0] * q.m[1] * q.m[2];
     const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (id >= tot) return;
     const int ix = (int)(id % q.m[0]);
     const int iy = (int)((id / q.m[0]) % q.m[1]);
     const int iz = (int)(id / ((long long)q.m[0] * q.m[1]));
-    oct[id] = entry_from_reps(comp, axis_reps(ix, tg.n[0], tg.P[0], tg.pbc[0]),
+    oct[blockIdx.y * tot + id] = entry_from_reps(comp, axis_reps(ix, tg.n[0], tg.P[0], tg.pbc[0]),
                               axis_reps(iy, tg.n[1], tg.P[1], tg.pbc[1]),
                               axis_reps(iz, tg.n[2], tg.P[2], tg.pbc[2]), tg);
 }
@@ -418,17 +420,23 @@ hipError_t build_kernel_spectrum(const Grid& g, const TensorGeom& tg, float* K, 
     for (int a = 0; a < 3; ++a) q.m[a] = tg.pbc[a] ? tg.n[a] / 2 + 1 : tg.n[a];
     const long long otot = (long long)q.m[0] * q.m[1] * q.m[2];
     double* oct = nullptr;
-    TRY(hipMalloc(&buf, sizeof(double2) * tot));
-    TRY(hipMalloc(&oct, sizeof(double) * otot));
-    TRY(hipMalloc(&mx, 2 * sizeof(unsigned long long)));
+    // small grids: the octants of all components in one launch, whose time is
+    // that of one offset; larger ones one by one, in the room of one
+    const int nc = otot <= 65536 ? ncomp : 1;
+    // (one allocation for the grid, the octants and the residue's maxima)
+    TRY(hipMalloc(&buf, sizeof(double2) * tot + sizeof(double) * nc * otot + 2 * sizeof(unsigned long long)));
+    oct = (double*)(buf + tot);
+    mx = (unsigned long long*)(oct + nc * otot);
     TRY(make_tw64(Px, &twx));
     TRY(make_tw64(Py, &twy));
     TRY(make_tw64(Pz, &twz));
     for (int c = 0; c < ncomp; ++c) {
         const int blocks = (int)((tot + TT - 1) / TT);
-        hipLaunchKernelGGL(tensor_octant_kernel, dim3((int)((otot + TT - 1) / TT)), dim3(TT), 0, s, oct, c, tg, q);
-        TRY(hipGetLastError());
-        hipLaunchKernelGGL(tensor_grid_kernel, dim3(blocks), dim3(TT), 0, s, buf, oct, c, tg, q);
+        if (c % nc == 0) {
+            hipLaunchKernelGGL(tensor_octant_kernel, dim3((int)((otot + TT - 1) / TT), nc), dim3(TT), 0, s, oct, c, tg, q);
+            TRY(hipGetLastError());
+        }
+        hipLaunchKernelGGL(tensor_grid_kernel, dim3(blocks), dim3(TT), 0, s, buf, oct + (c % nc) * otot, c, tg, q);
         TRY(hipGetLastError());
         TRY(fft_axis_f64(buf, Px, Py, Pz, 0, twx, s));
         TRY(fft_axis_f64(buf, Px, Py, Pz, 1, twy, s));
@@ -452,8 +460,6 @@ hipError_t build_kernel_spectrum(const Grid& g, const TensorGeom& tg, float* K, 
     if (resid_out) *resid_out = worst;
 done:
     if (buf) (void)hipFree(buf);
-    if (oct) (void)hipFree(oct);
-    if (mx) (void)hipFree(mx);
     if (twx) (void)hipFree(twx);
     if (twy) (void)hipFree(twy);
     if (twz) (void)hipFree(twz);
