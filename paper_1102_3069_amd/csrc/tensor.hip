@@ -164,31 +164,20 @@ struct Reps {
     double w[2];
 };
 
-// offsets that one FFT-grid index stands for along an axis
-__device__ Reps axis_reps(int idx, int n, int P, int periodic) {
+// the offsets that a signed offset d along an axis stands for: itself, or on a
+// periodic axis the nearest one, where n / 2 is the mean of n / 2 and -n / 2
+__device__ Reps axis_reps(int d, int n, int periodic) {
     Reps r;
-    r.n = 0;
-    if (!periodic) {
-        if (idx < n) { r.n = 1; r.off[0] = idx; r.w[0] = 1.0; }
-        else if (idx > P - n) { r.n = 1; r.off[0] = idx - P; r.w[0] = 1.0; }
-        return r;
-    }
-    int q = idx % n;
+    r.n = 1; r.off[0] = d; r.w[0] = 1.0;
+    if (!periodic) return r;
+    int q = ((d % n) + n) % n;
     if (n % 2 == 0 && q == n / 2) {
         r.n = 2; r.off[0] = n / 2; r.off[1] = -(n / 2); r.w[0] = r.w[1] = 0.5;
         return r;
     }
     if (q > n / 2) q -= n;
-    r.n = 1; r.off[0] = q; r.w[0] = 1.0;
+    r.off[0] = q;
     return r;
-}
-
-// periodic reduction of an arbitrary signed offset (for the offset query)
-__device__ Reps offset_reps(int d, int n, int periodic) {
-    Reps r;
-    if (!periodic) { r.n = 1; r.off[0] = d; r.w[0] = 1.0; return r; }
-    int q = ((d % n) + n) % n;
-    return axis_reps(q, n, n, 1);
 }
 
 __device__ double entry_from_reps(int comp, const Reps& rx, const Reps& ry, const Reps& rz,
@@ -217,9 +206,9 @@ __global__ void tensor_octant_kernel(double* oct, int comp0, TensorGeom tg, Octa
     const int ix = (int)(id % q.m[0]);
     const int iy = (int)((id / q.m[0]) % q.m[1]);
     const int iz = (int)(id / ((long long)q.m[0] * q.m[1]));
-    oct[blockIdx.y * tot + id] = entry_from_reps(comp, axis_reps(ix, tg.n[0], tg.P[0], tg.pbc[0]),
-                              axis_reps(iy, tg.n[1], tg.P[1], tg.pbc[1]),
-                              axis_reps(iz, tg.n[2], tg.P[2], tg.pbc[2]), tg);
+    oct[blockIdx.y * tot + id] = entry_from_reps(comp, axis_reps(ix, tg.n[0], tg.pbc[0]),
+                              axis_reps(iy, tg.n[1], tg.pbc[1]),
+                              axis_reps(iz, tg.n[2], tg.pbc[2]), tg);
 }
 
 // place of FFT-grid index idx among the non-negative offsets (-1: the zero
@@ -267,9 +256,9 @@ __global__ void tensor_grid_kernel(double2* out, const double* oct, int comp, Te
 __global__ void tensor_offsets_kernel(const int32_t* offs, long long count, double* out, TensorGeom tg) {
     const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (id >= count) return;
-    const Reps rx = offset_reps(offs[3 * id], tg.n[0], tg.pbc[0]);
-    const Reps ry = offset_reps(offs[3 * id + 1], tg.n[1], tg.pbc[1]);
-    const Reps rz = offset_reps(offs[3 * id + 2], tg.n[2], tg.pbc[2]);
+    const Reps rx = axis_reps(offs[3 * id], tg.n[0], tg.pbc[0]);
+    const Reps ry = axis_reps(offs[3 * id + 1], tg.n[1], tg.pbc[1]);
+    const Reps rz = axis_reps(offs[3 * id + 2], tg.n[2], tg.pbc[2]);
     for (int c = 0; c < 6; ++c) out[6 * id + c] = entry_from_reps(c, rx, ry, rz, tg);
 }
 
