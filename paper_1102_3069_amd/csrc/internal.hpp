@@ -299,7 +299,8 @@ hipError_t launch_row_inv(const Grid& g, const Phys& p, const FftPlan& px, const
                           float2* S, const StageArgs& sa, DevState* st, hipStream_t s);
 hipError_t launch_col(const ColArgs& a, DevState* st, int mode, hipStream_t s);
 hipError_t launch_ctrl_fixed(DevState* st, int evals, int steps, hipStream_t s);
-// progress (pinned host memory): 2 nattempt + done after each step or attempt
+// progress (pinned host memory): 2 nattempt + done, at the end of a run and after
+// every kPublishEvery-th attempt
 hipError_t launch_ctrl_dm(DevState* st, unsigned long long* progress, hipStream_t s);
 hipError_t launch_ctrl_dm_accept(DevState* st, int evals, unsigned long long* progress, hipStream_t s);
 hipError_t launch_ctrl_dp45(DevState* st, unsigned long long* progress, hipStream_t s);

@@ -552,14 +552,20 @@ llg_status restore_done(llg_solver* s, int was) {
 // host keeps kAhead graphs queued, so the device never waits for the host,
 // and at most kAhead - 1 graphs are launched past the end (they do nothing:
 // every kernel of a step returns while the flag is set, but each costs its
-// launches; chunks of eight wasted up to fifteen).  Twice the publishing
-// interval keeps three or more queued: 69 attempts at 512 x 512 12.81 -> 12.65
-// ms against every attempt published and three ahead, 10 at 2048 x 2048 26.35
-// -> 26.46; every fourth and twelve ahead 13.16 and 26.63.  Should the stream run dry
-// without the expected count (a run that ended on a non-finite value between
-// two attempts), the wait below ends too.
+// launches; chunks of eight wasted up to fifteen).  One more than the
+// publishing interval: one graph is queued behind the running one while the
+// host reacts.  us per run of four to five attempts and of many, at (published
+// every, ahead) of (3, 4), (3, 6), (2, 3) and (1, 2):
+//   64 x 64      378  470  323  320     11910  12000  12070  11720
+//   512 x 512    623  764  529  532     11410  11550  11390  11560
+//   1024 x 1024 1574 1889 1366 1370     19570  19880  19270  19350
+//   20 x 20 x 5                         20600  20700  20710  21040
+// and 400 attempts at 512 x 512, tuned, 183.0 us each published every third
+// time, 183.7 every second.  Should the stream run dry without the expected
+// count (a run that ended on a non-finite value between two attempts), the
+// wait below ends too.
 llg_status launch_until_done(llg_solver* s, hipGraphExec_t exec, long long base, long long max_launches) {
-    constexpr long long kAhead = 2 * kPublishEvery;
+    constexpr long long kAhead = kPublishEvery + 1;
     volatile unsigned long long* progress = s->progress;
     *progress = (unsigned long long)base << 1;
     long long launched = 0;
