@@ -31,6 +31,13 @@ namespace {
 
 constexpr int kRowThreads = 768;   // launch bound of the row kernels (at most twelve wavefronts)
 
+// Kernels start on 1 KB, not 256 bytes, so that a kernel's speed does not hang
+// on the size of those before it in the object: the same instructions of the
+// 3D row kernels 0x100 further on took 256 x 256 x 64 thermal Heun from 4474 to
+// 4534 us per 10 steps (aligned 4481), 1000 x 600 RK4 1746 and 1757 (1743);
+// 4 KB measured the same as 1 KB.
+constexpr int kKernelAlign = 1024;
+
 __device__ __forceinline__ float2 mk2(float x, float y) { float2 r; r.x = x; r.y = y; return r; }
 
 // Hermitian partner Z[(L - k) mod L] of element i of lane lg (k = lg + P i),
@@ -374,7 +381,7 @@ __device__ __forceinline__ void row_fwd_body(const Grid& g, const float2* __rest
 }
 
 template <int PX, int E2, int NQ, bool XPER, bool NAT>
-__global__ __launch_bounds__((RowSplit<PX, E2, NQ>::NT)) void row_fwd_fast(Grid g, const float2* __restrict__ twx,
+__global__ __attribute__((aligned(kKernelAlign))) __launch_bounds__((RowSplit<PX, E2, NQ>::NT)) void row_fwd_fast(Grid g, const float2* __restrict__ twx,
                                                             float2* __restrict__ S, FwdArgs fa,
                                                             DevState* __restrict__ st) {
     extern __shared__ char dyn_lds[];
@@ -962,7 +969,7 @@ __device__ __forceinline__ void row_inv_body(const Grid& g, const Phys& p, const
 }
 
 template <int PX, int E2, int NQ, bool XPER, bool NAT>
-__global__ __launch_bounds__((RowSplit<PX, E2, NQ>::NT)) void row_inv_fast(Grid g, Phys p, const float2* __restrict__ twx,
+__global__ __attribute__((aligned(kKernelAlign))) __launch_bounds__((RowSplit<PX, E2, NQ>::NT)) void row_inv_fast(Grid g, Phys p, const float2* __restrict__ twx,
                                                             float2* __restrict__ S, StageArgs sa,
                                                             DevState* __restrict__ st) {
     extern __shared__ char dyn_lds[];
@@ -1289,7 +1296,7 @@ __device__ __forceinline__ void col2d_body(const Col2dArgs& a, DevState* __restr
 }
 
 template <int L, int E, int NQ>
-__global__ __launch_bounds__((ColSplit<L, E, NQ>::NT)) void col2d_fast(Col2dArgs a, DevState* __restrict__ st) {
+__global__ __attribute__((aligned(kKernelAlign))) __launch_bounds__((ColSplit<L, E, NQ>::NT)) void col2d_fast(Col2dArgs a, DevState* __restrict__ st) {
     extern __shared__ char dyn_lds[];
     const int b = touch_args<sizeof(Col2dArgs)>(blockIdx.x);
     col2d_body<L, E, NQ>(a, st, xcd_remap_blocks(b, gridDim.x), dyn_lds);
@@ -1343,7 +1350,7 @@ constexpr int kParts = 5;
 // class (same compiled variant); block b works on film map[b].x, local
 // block map[b].y of that film
 template <int PX, int E2, int NQ>
-__global__ __launch_bounds__((RowSplit<PX, E2, NQ>::NT)) void row_fwd_group(const FilmRow* __restrict__ films,
+__global__ __attribute__((aligned(kKernelAlign))) __launch_bounds__((RowSplit<PX, E2, NQ>::NT)) void row_fwd_group(const FilmRow* __restrict__ films,
                                                              const int2* __restrict__ map) {
     extern __shared__ char dyn_lds[];
     const int2 m = map[blockIdx.x];
@@ -1353,7 +1360,7 @@ __global__ __launch_bounds__((RowSplit<PX, E2, NQ>::NT)) void row_fwd_group(cons
 }
 
 template <int PX, int E2, int NQ>
-__global__ __launch_bounds__((RowSplit<PX, E2, NQ>::NT)) void row_inv_group(const FilmRow* __restrict__ films,
+__global__ __attribute__((aligned(kKernelAlign))) __launch_bounds__((RowSplit<PX, E2, NQ>::NT)) void row_inv_group(const FilmRow* __restrict__ films,
                                                              const int2* __restrict__ map) {
     extern __shared__ char dyn_lds[];
     const int2 m = map[blockIdx.x];
@@ -1363,7 +1370,7 @@ __global__ __launch_bounds__((RowSplit<PX, E2, NQ>::NT)) void row_inv_group(cons
 }
 
 template <int L, int E, int NQ>
-__global__ __launch_bounds__((ColSplit<L, E, NQ>::NT)) void col_group(const FilmCol* __restrict__ films,
+__global__ __attribute__((aligned(kKernelAlign))) __launch_bounds__((ColSplit<L, E, NQ>::NT)) void col_group(const FilmCol* __restrict__ films,
                                                          const int2* __restrict__ map) {
     extern __shared__ char dyn_lds[];
     const int2 m = map[blockIdx.x];
