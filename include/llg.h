@@ -113,8 +113,11 @@ const char *llg_last_error(const llg_solver *s);
  * `pbc_images` (>= 0) periodic images are added per periodic axis on each
  * side.  Open axes are zero padded to an FFT length >= 2n made of the
  * factors 2, 3, 5, 7 (Sec. 3.3): the shortest one, or the next one with
- * compiled kernels; periodic axes keep their length, or are padded likewise
- * (the kernel continued periodically) where it has no compiled kernels.
+ * compiled kernels where that pays; periodic axes keep their length, or are
+ * padded likewise (the kernel continued periodically) where it has no
+ * compiled kernels.  Where only this lengthening takes the spectra beyond the
+ * static array of llg_eval_heff_noalloc, their room (less than 200 MB) is
+ * allocated here, whether that call is made or not.
  * Invalidates m and the demag kernel.
  * LLG_E_UNSUPPORTED if a padded length exceeds the library's limits
  * (x: 2048, y and z: 4096; x up to 4096 for one-cell-thick films whose
@@ -315,13 +318,14 @@ llg_status llg_autotune_attempts(llg_solver *s, double max_err, double dt0, int 
                                  int n_out, int *choice);
 llg_status llg_set_variants(llg_solver *s, int row_var, int col_var);
 /* The solver's (row, column) variant pair.  LLG_E_UNSUPPORTED unless the
- * geometry is 2D with compiled lengths. */
+ * geometry is 2D and its shortest padded lengths are compiled. */
 llg_status llg_get_variants(llg_solver *s, int *row_var, int *col_var);
 /* Shape of a compiled variant: kind 0 a row length Px, kind 1 a column half
  * length L = Py/2; *elems receives the elements each lane holds in a
  * transform, *classes the number of frequency classes each padded
  * transform is split into (2 or 4; one lane group per class).  LLG_E_ARG if
- * there is no such variant.  Needs no device. */
+ * there is no such variant.  Needs no device.  Variant numbers belong to a
+ * build of the library: pairs kept from another one are looked up here. */
 llg_status llg_variant_shape(int kind, int length, int variant, int *elems, int *classes);
 
 /* ---- diagnostics ------------------------------------------------------------
